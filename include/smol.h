@@ -353,8 +353,9 @@ int smol_image_geometry_ex(int32_t width, int32_t height, int32_t yuv420, const 
  *               bytes and the chroma span at most 992, else direct). For I420 only 0, 1 and 4 are
  *               valid; 4 fails with SMOL_ERR_UNSUPPORTED past those limits
  *   band_rows   output rows per band in the LDS-staged kernels (1..64); for
- *               the row-streaming kernel, 1 or 2 sets how many output rows
- *               ahead of the interpolated one each wave loads
+ *               the strided walk of the row-streaming RGB kernel (row_order),
+ *               1 or 2 sets how many output rows ahead of the interpolated
+ *               one each wave loads
  *   lds_budget  bytes of LDS one workgroup may use (4096..163840, and at most
  *               the device's per-workgroup limit)
  *   workgroups_per_cu  cap on the resident workgroups per compute unit

@@ -384,6 +384,58 @@ struct Plan {
     int f16;
 };
 
+// The column strips of a row-streaming launch, at least `least` of them. A
+// crop of more than kStripCols columns splits into strips of 256 columns (two
+// column pairs per lane) or, where that leaves an odd number of 128-column
+// halves, of 128 (one pair per lane), which fill every lane and start at whole
+// 128-byte lines of fp16 output; the last strip ends at the last column and
+// overlaps its neighbour. More strips than that (long source spans) have equal
+// widths. 32 frames of 720p to 640 x 640: 37.0 us in 5 strips of 128, 40.7 in
+// 3 of 216, 43.6 in 4 of 160 (61 us on the register-gather kernel).
+void plan_strips(int Cw, int least, int *strips, int *strip_w)
+{
+    const int halves = (Cw + 127) / 128;
+    const int width = Cw <= smol::kStripCols ? Cw : halves % 2 ? 128 : smol::kStripCols;
+    *strips = (Cw + width - 1) / width;
+    *strip_w = width;
+    if (least > *strips) {
+        *strip_w = ((Cw + least - 1) / least + 3) & ~3;
+        *strips = (Cw + *strip_w - 1) / *strip_w;
+    }
+}
+
+// Source columns that any `cols` consecutive columns of the crop read, at
+// most: the taps of columns c and c + cols - 1 are no further apart than
+// ceil((cols - 1) W / Wr), and each column reads two.
+int64_t strip_span(const Desc &d, int64_t whole, int Cw, int cols)
+{
+    if (cols == Cw)
+        return whole;
+    return std::min<int64_t>(whole, udiv((int64_t)(cols - 1) * d.W, d.Wr) + 3);
+}
+
+// Strips for a batch whose strips may span up to max_span source columns:
+// the fewest that fit, in a.strips and a.strip_w; returns the widest strip's
+// span, or 0 if strips of kStripMinCols columns do not fit either. `whole`:
+// the crop's widest span; cols_of(d): the crop's span of one image.
+template <class Whole>
+int64_t fit_strips(const std::vector<Desc> &descs, int Cw, int64_t whole, int64_t max_span,
+                   Whole span_of, BatchArgs *a)
+{
+    int least = 1;
+    for (;; ++least) {
+        plan_strips(Cw, least, &a->strips, &a->strip_w);
+        int64_t span = a->strips == 1 ? whole : 0;
+        if (a->strips > 1)
+            for (const Desc &d : descs)
+                span = std::max(span, strip_span(d, span_of(d), Cw, a->strip_w));
+        if (span <= max_span)
+            return span;
+        if (a->strip_w <= smol::kStripMinCols)
+            return 0;
+    }
+}
+
 size_t align16(size_t v) { return (v + 15) & ~(size_t)15; }
 
 // LDS layout of the RGB kernel: two buffers per workgroup, each
@@ -494,6 +546,14 @@ int run_batch(const std::vector<Desc> &descs, size_t first, size_t count, int no
         a.interleave = pl.f16 != SMOL_OUT_U8 &&
                        (order == 2 || (order == 0 && uniform && pl.path == smol::PATH_ROWS &&
                                        a.row_groups >= 4));
+        // Whole-line stores: rows of 16-byte multiples, at least one line
+        // long, that are not whole lines themselves, in planes of whole lines.
+        const long long rb = 2LL * a.Cw;
+        a.lines = pl.path == smol::PATH_ROWS && pl.f16 == SMOL_OUT_F16 && !a.interleave &&
+                  !a.nhwc && a.strips == 1 && rb % 16 == 0 && rb >= 128 && rb % 128 != 0 &&
+                  rb * a.Ch % 128 == 0 && ((uintptr_t)a.out & 127) == 0;
+        if (a.lines)
+            pl.lds_bytes += 3 * smol::kLineRing;
     }
     if (pl.path == smol::PATH_LDS || pl.path == smol::PATH_GATHER || rows) {
         a.wpg = rows ? smol::kRowsMaxWavesPerGroup : 1;
@@ -514,7 +574,8 @@ int run_batch(const std::vector<Desc> &descs, size_t first, size_t count, int no
         if (rows) {
             // Waves per compute unit (the tuning knob counts waves here).
             int waves = per_cu * a.wpg;
-            items = (long long)n * a.Ch;
+            items = (long long)n * a.Ch;  // rows of one column strip
+            const int S = a.strips;
             if (forced > 0) {
                 waves = std::min(waves, forced);
             } else {
@@ -524,7 +585,7 @@ int run_batch(const std::vector<Desc> &descs, size_t first, size_t count, int no
                 // multiples of 4 waves per compute unit (a wave's set-up and
                 // first load cost about a row; 7,168 rows of 224 columns take
                 // 8.1 us on 5,120 waves and 6.7 us on 2,048).
-                const long long by_rows = items / kRowsMinPerWave / di.cus;
+                const long long by_rows = items * S / kRowsMinPerWave / di.cus;
                 if (by_rows < waves)
                     waves = (int)std::min<long long>(waves,
                                                      std::max<long long>(4, by_rows & ~3LL));
@@ -532,7 +593,8 @@ int run_batch(const std::vector<Desc> &descs, size_t first, size_t count, int no
             // Workgroups of 4 (or 2) waves when that count allows, so each
             // compute unit still holds at most `waves` of them.
             a.wpg = waves % 4 == 0 ? 4 : waves % 2 == 0 ? 2 : 1;
-            long long w = std::min<long long>(items, (long long)di.cus * waves);
+            long long w = std::min<long long>(
+                items, std::max<long long>(1, (long long)di.cus * waves / S));
             if (w >= a.wpg)
                 w -= w % a.wpg;
             else
@@ -588,8 +650,8 @@ int run_batch(const std::vector<Desc> &descs, size_t first, size_t count, int no
         info->path = pl.path == smol::PATH_YUV_ROWS ? smol::PATH_ROWS : pl.path;
         info->band_rows = pl.path == smol::PATH_LDS ? pl.R : 0;
         info->lds_bytes = (int)pl.lds_bytes;
-        info->grid = pl.grid;
-        info->work_items = items;
+        info->grid = pl.grid * (rows ? a.strips : 1);
+        info->work_items = items * (rows ? a.strips : 1);
     }
     info->uploaded_descriptors |= uniform ? 0 : 1;
 
@@ -881,12 +943,11 @@ static int rgb_batch(const uint8_t *src, int64_t src_bytes, const int64_t *offse
         DeviceInfo di;
         const bool have_dev =
             hipGetDevice(&device) == hipSuccess && device_info(device, &di) == hipSuccess;
-        const int col_iters = p->crop_w <= 128 ? 1 : p->crop_w <= 256 ? 2 : 4;
         // A staged row: up to 15 bytes before the span (16-byte aligned
         // chunks), the span, and the 12-byte read of the last column's taps,
         // in groups of 64 chunks (1 KiB).
-        const int64_t groups = (max_span + 32 + 1023) / 1024;
-        const int64_t lds_bytes = 2 * 1024 * (groups <= 1 ? 1 : groups <= 2 ? 2 : 4);
+        int64_t groups = (max_span + 32 + 1023) / 1024;
+        int64_t lds_bytes = 2 * 1024 * (groups <= 1 ? 1 : groups <= 2 ? 2 : 4);
         const int64_t budget = std::min<int64_t>(
             have_dev ? di.lds_per_block : 65536,
             g_lds_budget.load() > 0 ? g_lds_budget.load() : INT64_MAX);
@@ -897,18 +958,26 @@ static int rgb_batch(const uint8_t *src, int64_t src_bytes, const int64_t *offse
             nruns += (i == 0 || descs[(size_t)i].safe != descs[(size_t)i - 1].safe) ? 1 : 0;
         }
         runs_ok = nruns <= 3;
-        const bool rows_ok = have_dev && p->crop_w <= 128 * smol::kRowsMaxColIters &&
+        const bool rows_ok = have_dev && p->crop_w <= smol::kRowsMaxCols &&
                              groups <= smol::kRowsMaxGroups && lds_bytes <= budget;
         if (forced == smol::PATH_ROWS && !rows_ok)
             return fail(SMOL_ERR_UNSUPPORTED, "row-streaming path forced but the crop width or "
                         "source span does not fit (crop_w <= %d, span + 32 <= %d bytes, "
                         "%lld bytes of LDS)",
-                        128 * smol::kRowsMaxColIters, 1024 * smol::kRowsMaxGroups,
+                        smol::kRowsMaxCols, 1024 * smol::kRowsMaxGroups,
                         (long long)lds_bytes);
-        if (rows_ok && (forced == smol::PATH_ROWS ||
-                        (forced == smol::PATH_AUTO && any_safe && runs_ok))) {
+        const bool strips_ok = rows_ok;
+        int64_t strip_cols = 0;
+        if (strips_ok && (forced == smol::PATH_ROWS ||
+                          (forced == smol::PATH_AUTO && any_safe && runs_ok)))
+            strip_cols = fit_strips(descs, p->crop_w, max_span / 3,
+                                    (1024 * smol::kRowsMaxGroups - 32) / 3,
+                                    [](const Desc &d) { return (int64_t)d.span / 3; }, &a);
+        if (strip_cols > 0) {
+            groups = (3 * strip_cols + 32 + 1023) / 1024;
+            lds_bytes = 2 * 1024 * (groups <= 1 ? 1 : groups <= 2 ? 2 : 4);
             Plan pr{smol::PATH_ROWS, 0, (size_t)lds_bytes, 0, f16};
-            a.col_iters = col_iters;
+            a.col_iters = a.strip_w <= 128 ? 1 : 2;
             a.row_groups = (int)(lds_bytes / 2048);
             // Prefetch depth (band_rows 1 or 2 forces it): long staged rows
             // keep one row in flight per wave, short ones two.
@@ -1104,16 +1173,23 @@ static int yuv_batch(const uint8_t *src, int64_t src_bytes, const int64_t *y_off
     // Row-streaming kernel: staged luma rows of at most 2 KiB and chroma rows
     // of at most 1 KiB (span + 32 bytes), crops up to 512 columns; frames
     // whose planes' chunks cross an end of src go to the direct kernel.
-    const bool rows_ok = p->crop_w <= 128 * smol::kRowsMaxColIters && max_yspan + 32 <= 2048 &&
+    const bool rows_ok = p->crop_w <= smol::kRowsMaxCols && max_yspan + 32 <= 2048 &&
                          max_cspan + 32 <= 1024;
+    const bool strips_ok = rows_ok;
     if (forced == smol::PATH_ROWS && !rows_ok)
         return fail(SMOL_ERR_UNSUPPORTED, "row-streaming I420 path forced but the crop is wider "
                     "than %d columns, the luma span exceeds 2016 bytes or the chroma span 992",
-                    128 * smol::kRowsMaxColIters);
-    if (rows_ok && (forced == smol::PATH_ROWS || forced == smol::PATH_AUTO)) {
-        a.col_iters = p->crop_w <= 128 ? 1 : p->crop_w <= 256 ? 2 : 4;
+                    smol::kRowsMaxCols);
+    const int64_t max_strip = max_cspan + 32 <= 1024 ? 2048 - 32 : 2 * (1024 - 32 - 2);
+    const int64_t yspan =
+        strips_ok && (forced == smol::PATH_ROWS || forced == smol::PATH_AUTO)
+            ? fit_strips(descs, p->crop_w, max_yspan, max_strip,
+                         [](const Desc &d) { return (int64_t)d.span; }, &a)
+            : 0;
+    if (yspan > 0) {
+        a.col_iters = a.strip_w <= 128 ? 1 : 2;
         // luma segments of 1 or 2 KiB, six chroma segments of 1 KiB per wave
-        a.row_groups = max_yspan + 32 <= 1024 ? 1 : 2;
+        a.row_groups = yspan + 32 <= 1024 ? 1 : 2;
         const Plan pr{smol::PATH_YUV_ROWS, 0, (size_t)(2 * a.row_groups + 6) * 1024, 0, f16};
         auto rows = [f16](const BatchArgs &x, const Plan &q, void *s, void *done) {
             return smol::launch_yuv_rows(x, f16, q.lds_bytes, s, done);

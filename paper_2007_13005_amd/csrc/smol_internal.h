@@ -48,8 +48,12 @@ struct BatchArgs {
     int32_t grid;        // workgroups of a persistent launch (LDS kernels)
     int32_t stage_bytes; // bytes of one of the two LDS buffers of a wave
     int32_t row_groups;  // 1 KiB chunk groups per staged source row (row-streaming kernel)
-    int32_t col_iters;   // column pairs per lane: 1, 2 or 4 (row-streaming kernel)
-    int32_t prefetch;    // rows loaded ahead of the one interpolated: 1 or 2 (row streaming)
+    int32_t col_iters;   // column pairs per lane: 1 or 2 (row-streaming kernel)
+    // Row streaming: the crop's columns are `strips` strips of strip_w (the
+    // last one ends at the last column), one per workgroup row of the grid.
+    int32_t strips, strip_w;
+    int32_t lines;       // 1: rows leave as whole 128-byte lines (contiguous walk, fp16 NCHW)
+    int32_t prefetch;    // rows loaded ahead of the one interpolated: 1 or 2 (strided RGB walk)
     int32_t interleave;  // row streaming: wave q takes rows q, q + G, ... (else a range)
     int32_t exact;       // 1: operation-by-operation fp32 arithmetic (row-streaming kernel)
     int32_t wpg;         // row streaming: waves per workgroup (grid = waves / wpg)
@@ -75,10 +79,20 @@ enum Path { PATH_AUTO = 0, PATH_DIRECT = 1, PATH_LDS = 2, PATH_GATHER = 3, PATH_
 // Pseudo path of the I420 row-streaming kernel in run_batch (reported as PATH_ROWS).
 constexpr int PATH_YUV_ROWS = 5;
 
-// Row-streaming kernel limits: crops up to 2 * 64 * kRowsMaxColIters columns,
-// staged source rows (span + 32 bytes) up to kRowsMaxGroups KiB.
-constexpr int kRowsMaxColIters = 4;
+// Row-streaming kernel limits: strips of up to kStripCols columns, staged
+// source rows (span + 32 bytes) up to kRowsMaxGroups KiB. A forced row-streaming
+// path takes crops up to kRowsMaxCols columns whose whole span fits; the
+// automatic choice also crops up to kStripsMaxCols columns and longer spans, in
+// strips of at least kStripMinCols columns.
+constexpr int kRowsMaxCols = 512;
+constexpr int kStripCols = 256;
+constexpr int kStripsMaxCols = 2048;
+constexpr int kStripMinCols = 48;
+constexpr int kStripsMinRows = 64;
 constexpr int kRowsMaxGroups = 4;
+// Bytes of a plane's output ring in a wave's LDS slot (whole-line stores): a row
+// of kStripCols fp16 elements and the line before it.
+constexpr int kLineRing = 1024;
 // Waves per workgroup of the row-streaming kernels (each wave independent).
 constexpr int kRowsMaxWavesPerGroup = 4;
 
@@ -162,7 +176,8 @@ int launch_rgb_direct(const BatchArgs &a, int out_type, void *stream, void *done
 int launch_rgb_lds(const BatchArgs &a, int out_f16, size_t lds_bytes, void *stream, void *done);
 int launch_rgb_gather(const BatchArgs &a, int out_f16, size_t lds_bytes, void *stream, void *done);
 // Row-streaming launches: `lds_bytes` is one wave's slot; a workgroup holds
-// a.wpg waves and a.grid is the number of waves (a multiple of a.wpg).
+// a.wpg waves and a.grid is the number of waves per column strip (a multiple
+// of a.wpg).
 int launch_rgb_rows(const BatchArgs &a, int out_f16, size_t lds_bytes, void *stream, void *done);
 // Resident workgroups of a.wpg waves per compute unit.
 int occupancy_rgb_rows(const BatchArgs &a, int out_f16, size_t lds_bytes, int *blocks_per_cu);

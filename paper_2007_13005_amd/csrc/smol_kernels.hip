@@ -807,7 +807,8 @@ const void *rows_kernel(const BatchArgs &a, int f16)
 
 int launch_rgb_rows(const BatchArgs &a, int out_f16, size_t lds_bytes, void *stream, void *done)
 {
-    return launch_one(rows_kernel(a, out_f16), dim3((unsigned)(a.grid / a.wpg)), dim3(64 * a.wpg),
+    return launch_one(rows_kernel(a, out_f16),
+                      dim3((unsigned)(a.grid / a.wpg), (unsigned)a.strips), dim3(64 * a.wpg),
                       lds_bytes * a.wpg, a, stream, done);
 }
 
@@ -877,14 +878,14 @@ const void *yuv_rows_kernel_for(const BatchArgs &a, int f16)
 // 2 J columns (the kernel's yuv_col_table_bytes).
 static size_t yuv_rows_table_lds(const BatchArgs &a, bool uniform)
 {
-    const size_t J = a.col_iters <= 1 ? 1 : a.col_iters <= 2 ? 2 : 4;
+    const size_t J = a.col_iters <= 1 ? 1 : 2;
     return uniform && a.wpg > 1 ? 2 * J * 64 * 32 : 0;
 }
 
 int launch_yuv_rows(const BatchArgs &a, int out_f16, size_t lds_bytes, void *stream, void *done)
 {
-    return launch_one(yuv_rows_kernel_for(a, out_f16), dim3((unsigned)(a.grid / a.wpg)),
-                      dim3(64 * a.wpg), lds_bytes * a.wpg + yuv_rows_table_lds(a, !a.table), a,
+    return launch_one(yuv_rows_kernel_for(a, out_f16),
+                      dim3((unsigned)(a.grid / a.wpg), (unsigned)a.strips), dim3(64 * a.wpg), lds_bytes * a.wpg + yuv_rows_table_lds(a, !a.table), a,
                       stream, done);
 }
 

@@ -14,35 +14,38 @@ namespace smol {
 namespace {
 
 // ---------------------------------------------------------------------------
-// RGB, row streaming: one wave per workgroup, no barriers.
+// RGB, row streaming: independent waves, no barriers.
 //
-// Work items are output rows (image, row), image-major. With STRIDE = 0 wave
-// g takes the contiguous range [g*T/G, (g+1)*T/G) of the T rows; with
-// STRIDE = 1 it takes rows q, q + G, q + 2G, ... (q: g remapped so the waves
-// of one XCD take neighbouring rows), so the rows in flight on the chip at
-// any moment form one band of the output. For each output row the
-// wave loads the two source rows its vertical taps read -- only the crop's
-// source column span, as the 16-byte chunks that hold it, aligned in the
-// global address space, one coalesced 16-byte load per lane and 64 chunks --
-// into registers, two rows ahead of the row it interpolates (three register
-// sets in rotation), and writes a row's chunks into its LDS slot right after
-// interpolating the previous row. The bytes in flight live in registers, so a
-// compute unit keeps more loads outstanding than its LDS could stage, and
-// the compiler orders each LDS write after exactly the loads it needs.
+// Work items are output rows (image, row), image-major. On the contiguous walk
+// wave g takes the range [g*T/G, (g+1)*T/G) of the T rows; on the strided walk
+// it takes rows q, q + G, q + 2G, ... (q: g remapped so the waves of one XCD
+// take neighbouring rows), so the rows in flight on the chip at any moment
+// form one band of the output. For each output row the wave loads the two
+// source rows its vertical taps read -- only the crop's source column span, as
+// the 16-byte chunks that hold it, aligned in the global address space, one
+// coalesced 16-byte load per lane and 64 chunks -- into registers, one or two
+// rows ahead of the row it interpolates, and writes a row's chunks into its
+// LDS slot right after interpolating the previous row. The bytes in flight
+// live in registers, so a compute unit keeps more loads outstanding than its
+// LDS could stage, and the compiler orders each LDS write after exactly the
+// loads it needs.
+//
+// A wide crop, or one whose source span is long, runs as column strips side by
+// side (strip_start); a wave keeps to one strip.
 //
 // Only images whose chunks all lie inside src come here; the host sends the
 // others to the direct kernel. Lanes past a row's last chunk load that chunk
 // again (their copy lands past the row in the slot and is never read).
 //
-// A cursor steps the vertical half-pixel map incrementally with exact integer
-// arithmetic (the numerator grows by 2*H per output row, or by a precomputed
-// constant per strided step): no division per row but the one for the
-// weight.
+// The contiguous walk computes its rows' vertical taps 64 at a time, a row per
+// lane (row_records); the strided walk steps the vertical half-pixel map with
+// exact integer arithmetic (the numerator grows by a precomputed constant per
+// step): no division per row but the one for the weight.
 //
-// Lane l computes output columns c = 2l + 128j and c + 1 (j < J); their taps
-// (byte offset in the staged span, weight) stay in registers while the
-// horizontal geometry is unchanged. Each pixel's two horizontal taps are 6
-// bytes of a staged row, read as three aligned dwords and realigned.
+// Lane l computes 2J consecutive output columns (lane_col); their taps (byte
+// offset in the staged span, weight) stay in registers while the horizontal
+// geometry is unchanged. Each pixel's two horizontal taps are 6 bytes of a
+// staged row, read as three aligned dwords and realigned.
 //
 // The three lerps are always evaluated as defined, every product and sum
 // rounded on its own. EXACT selects the rest: 1 forms the normalisation as
@@ -62,7 +65,15 @@ struct RowImg {
 // against (or wait for) the vector-memory counter.
 typedef __attribute__((address_space(4))) const Desc ConstDesc;
 
-__device__ __forceinline__ RowImg row_img(const BatchArgs &a, int img)
+// The first crop column of column strip `strip` of a launch: strips of
+// a.strip_w columns side by side, the last one ending at the crop's last
+// column (where it overlaps its neighbour, both store the same values).
+__device__ __forceinline__ int strip_start(const BatchArgs &a, int strip)
+{
+    return min(strip * a.strip_w, a.Cw - a.strip_w);
+}
+
+__device__ __forceinline__ RowImg row_img(const BatchArgs &a, int img, int strip)
 {
     RowImg g;
     if (a.table) {
@@ -88,34 +99,67 @@ __device__ __forceinline__ RowImg row_img(const BatchArgs &a, int img)
         g.top = a.uni.top;
         g.xf = a.uni.xf;
         g.span = a.uni.span;
-            }
+    }
+    if (a.strips > 1) {
+        // the strip's own columns of the crop and the source span they read
+        g.left += strip_start(a, strip);
+        g.xf = axis_tap(g.left, g.W, g.Wr).x0;
+        g.span = 3 * (axis_tap(g.left + a.strip_w - 1, g.W, g.Wr).x1 - g.xf + 1);
+    }
     return g;
 }
 
-// First output column of the pair lane `lane` computes in column iteration
-// j: 2 * lane + 128 * j, clamped to the last pair (Cw - 2 for even Cw, the
-// last column for odd Cw). Lanes past the crop thus compute and store a
-// copy of the last pair, the same values to the same addresses: every lane
-// runs the same stores, with no branch around them, and the compiler can
-// count the memory operations in flight exactly (a branch that might skip
-// the stores would make it wait for them before every write to LDS).
-__device__ __forceinline__ int pair_col(int lane, int j, int Cw)
+// First of the strip's columns that lane `lane` computes: 2J consecutive
+// columns from 2 J lane on, clamped so that they end at the strip's last
+// column (cols >= 2J, or cols = 1 with J = 1). Lanes past the strip thus
+// compute and store columns that other lanes store as well, the same values
+// to the same addresses: every lane runs the same stores, with no branch
+// around them, and the compiler can count the memory operations in flight
+// exactly (a branch that might skip the stores would make it wait for them
+// before every write to LDS).
+template <int J>
+__device__ __forceinline__ int lane_col(int lane, int cols)
 {
-    return min(2 * lane + 128 * j, Cw - 2 + (Cw & 1));
+    return min(2 * J * lane, max(cols - 2 * J, 0));
 }
 
+// Column taps of the lane's 2J consecutive columns: one division for the first
+// (floor quotient and remainder of num = (2 (left + c) + 1) W - Wr by
+// den = 2 Wr), exact integer steps for the others. The weight rem / den
+// rounded to nearest fp32 comes from an fp64 product with RN(1 / den): the
+// product is within 2^-52 (relative) of the quotient, and no such quotient
+// (0 < rem < den <= 2^24) lies within 2^-49 (relative) of a midpoint between
+// fp32 values, so both round to the same fp32 value. (A tap computed on its
+// own costs about 60 instructions, and a wave of a ragged batch walks only a
+// dozen rows with them.)
 template <int J>
-__device__ __forceinline__ void row_taps(const RowImg &g, const int Cw, int (&cx)[J][2],
+__device__ __forceinline__ void row_taps(const RowImg &g, const int cols, int (&cx)[J][2],
                                          float (&cw)[J][2], int lane)
 {
+    const int den = 2 * g.Wr;
+    const double rcp = 1.0 / (double)den;
+    const long long num = (long long)(2 * (g.left + lane_col<J>(lane, cols)) + 1) * g.W - g.Wr;
+    // -den < num < 2^39; the double quotient's truncation is the exact floor
+    // (a non-integer quotient is at least 1 / den from the next integer)
+    int q = num < 0               ? -1
+            : num < 0x7fffffffLL ? (int)((unsigned)num / (unsigned)den)
+                                 : (int)((double)num / (double)den);
+    int rem = (int)(num - (long long)q * den);
+    // a crop of one column computes it twice
+    const int step = cols > 1 ? 2 * g.W : 0;
+    const int qs = step / den, rs = step - qs * den;
 #pragma unroll
     for (int j = 0; j < J; ++j)
 #pragma unroll
         for (int px = 0; px < 2; ++px) {
-            const int col = min(pair_col(lane, j, Cw) + px, Cw - 1);
-            const Tap t = axis_tap(g.left + col, g.W, g.Wr);
-            cx[j][px] = 3 * (t.x0 - g.xf);
-            cw[j][px] = t.w;
+            const bool low = q < 0, high = q >= g.W - 1;
+            cx[j][px] = 3 * ((low ? 0 : high ? g.W - 1 : q) - g.xf);
+            cw[j][px] = low || high ? 0.0f : (float)((double)rem * rcp);
+            q += qs;
+            rem += rs;
+            const bool carry = rem >= den;
+            rem -= carry ? den : 0;
+            q += carry ? 1 : 0;
         }
 }
 
@@ -195,7 +239,6 @@ struct StagedRows {
     u32x4 c0[G], c1[G];
     int sh0, sh1;
     float wy;
-    int y0, y1;  // the source rows
 };
 
 // The rows a wave walks: batch rows r0, r0 + d, r0 + 2d, ... as (image, crop
@@ -340,7 +383,8 @@ __device__ __forceinline__ void vcursor_tap(const VCursor &v, int &y0, int &y1, 
     }
 }
 
-// Load cursor: image, crop row, vertical map and the image's row addressing.
+// Load cursor of the strided RGB walk: image, crop row, vertical map and the
+// image's row addressing.
 struct RowCursor {
     int img, rr;
     VCursor v;
@@ -348,14 +392,13 @@ struct RowCursor {
     int pitch, span;
 };
 
-template <int STRIDE>
 __device__ __forceinline__ void cursor_image(RowCursor &c, const BatchArgs &a, int img, int rr,
                                              const RowStep &s)
 {
-    const RowImg g = row_img(a, img);
+    const RowImg g = row_img(a, img, (int)blockIdx.y);
     c.img = img;
     c.rr = rr;
-    vcursor_init<STRIDE>(c.v, a, g, rr, s);
+    vcursor_init<1>(c.v, a, g, rr, s);
     c.base = (uintptr_t)(a.src + g.off) + 3 * (uintptr_t)g.xf;
     c.pitch = g.pitch;
     c.span = g.span;
@@ -365,15 +408,8 @@ __device__ __forceinline__ void cursor_image(RowCursor &c, const BatchArgs &a, i
 // images `stride` bytes apart) moves the base address and steps the vertical
 // map; over a table it reads the new image's descriptor when the image
 // changes.
-template <int STRIDE>
 __device__ __forceinline__ void cursor_next(RowCursor &c, const BatchArgs &a, const RowStep &s)
 {
-    if (!STRIDE) {
-        vcursor_add(c.v, c.v.qs, c.v.rs);
-        if (++c.rr == s.Ch && c.img + 1 < a.n)
-            cursor_image<0>(c, a, c.img + 1, 0, s);
-        return;
-    }
     const int img0 = c.img;
     c.img += s.di;
     c.rr += s.dr;
@@ -386,7 +422,7 @@ __device__ __forceinline__ void cursor_next(RowCursor &c, const BatchArgs &a, co
         c.base += (uintptr_t)(c.img - img0) * (uintptr_t)a.stride;
         vcursor_add(c.v, wrapped ? c.v.qw : c.v.qs, wrapped ? c.v.rw : c.v.rs);
     } else if (c.img != img0) {
-        cursor_image<1>(c, a, c.img, c.rr, s);
+        cursor_image(c, a, c.img, c.rr, s);
     } else {
         vcursor_add(c.v, c.v.qs, c.v.rs);
     }
@@ -395,19 +431,14 @@ __device__ __forceinline__ void cursor_next(RowCursor &c, const BatchArgs &a, co
 // `repeat`: the row was loaded already (past the end of the wave's range);
 // every lane then loads the rows' first chunk, so the instruction stream is
 // unchanged but almost nothing is fetched.
-// NT: nontemporal loads, for walks that read each source row once (the
-// strided walk of large frames); a contiguous walk meets a source row again
-// when consecutive output rows share it (upscales, downscales by less than
-// 2, and the rows of an image's neighbours in the walk), and ordinary loads
-// let those reads hit in the caches.
-template <int G, int NT = 1>
+// Nontemporal loads: the strided walk of large frames reads each source row
+// once.
+template <int G>
 __device__ __forceinline__ void load_rows(StagedRows<G> &st, const RowCursor &c, int lane,
                                           bool repeat)
 {
     int y0, y1;
     vcursor_tap(c.v, y0, y1, st.wy);
-    st.y0 = y0;
-    st.y1 = y1;
     const uintptr_t r0 = c.base + (uintptr_t)y0 * (uintptr_t)c.pitch;
     const uintptr_t r1 = c.base + (uintptr_t)y1 * (uintptr_t)c.pitch;
     st.sh0 = (int)(r0 & 15);
@@ -426,13 +457,8 @@ __device__ __forceinline__ void load_rows(StagedRows<G> &st, const RowCursor &c,
         const uint32_t o0 = 16u * (uint32_t)min(64 * g + lane, last0);
         const uint32_t o1 = 16u * (uint32_t)min(64 * g + lane, last1);
         typedef const __attribute__((address_space(1))) u32x4 GlobalChunk;
-        if (NT) {
-            st.c0[g] = __builtin_nontemporal_load((GlobalChunk *)(p0 + o0));
-            st.c1[g] = __builtin_nontemporal_load((GlobalChunk *)(p1 + o1));
-        } else {
-            st.c0[g] = *(GlobalChunk *)(p0 + o0);
-            st.c1[g] = *(GlobalChunk *)(p1 + o1);
-        }
+        st.c0[g] = __builtin_nontemporal_load((GlobalChunk *)(p0 + o0));
+        st.c1[g] = __builtin_nontemporal_load((GlobalChunk *)(p1 + o1));
     }
 }
 
@@ -555,16 +581,29 @@ __device__ __forceinline__ void read_taps(uint32_t row0, uint32_t row1, const in
 // the loads they may overtake, so a wait for a load issued before a store
 // lasts until the store is done as well).
 // Output form of a row-streaming kernel instance (its FORM template
-// parameter): NHWC layout, odd crop width.
+// parameter): NHWC layout, crops of a single column, rows stored as whole
+// lines.
 constexpr int kFormNhwc = 1;
-constexpr int kFormOdd = 2;
+constexpr int kFormOne = 2;
+constexpr int kFormLines = 4;
 
-// A lane's output pairs of one row: per column pair and channel two fp32
-// words (F16 0), one word of two fp16 (F16 1) or the low half-word of one
-// word holding two uint8 (F16 2, uint8 output).
+// A lane's output pairs of one row: per channel, for every column pair, two
+// fp32 words (F16 0), one word of two fp16 (F16 1) or the low half-word of one
+// word holding two uint8 (F16 2, uint8 output). (One vector, not an array:
+// vector stores gathered from an array's elements keep the array in memory.)
 template <int F16, int J>
 struct RowOut {
-    uint32_t w[J][3][F16 ? 1 : 2];
+    static constexpr int kWords = F16 ? J : 2 * J;  // per channel
+    uint32_t __attribute__((ext_vector_type(3 * kWords))) w;
+    // word k of pair j (k = 0 unless fp32)
+    __device__ __forceinline__ uint32_t word(int ch, int j, int k = 0) const
+    {
+        return w[ch * kWords + (F16 ? j : 2 * j + k)];
+    }
+    __device__ __forceinline__ void set(int ch, int j, int k, uint32_t v)
+    {
+        w[ch * kWords + (F16 ? j : 2 * j + k)] = v;
+    }
 };
 
 template <int F16, int EXACT, int J>
@@ -575,145 +614,135 @@ __device__ __forceinline__ void pack_pair(RowOut<F16, J> &out, int j, const floa
         if (F16 == 2) {
             // clamped to [0, 255] and rounded to nearest even, into bytes 0
             // and 1 (v_cvt_pk_u8_f32 does clamp, round, convert and insert)
-            out.w[j][ch][0] = __builtin_amdgcn_cvt_pk_u8_f32(
-                o[ch][1], 1u, __builtin_amdgcn_cvt_pk_u8_f32(o[ch][0], 0u, 0u));
+            out.set(ch, j, 0,
+                    __builtin_amdgcn_cvt_pk_u8_f32(
+                        o[ch][1], 1u, __builtin_amdgcn_cvt_pk_u8_f32(o[ch][0], 0u, 0u)));
         } else if (F16 && !EXACT) {
             // The conversion may fuse with the last product (one rounding
             // to fp16 instead of two).
             typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
             const f16x2 h = {(_Float16)o[ch][0], (_Float16)o[ch][1]};
-            out.w[j][ch][0] = __builtin_bit_cast(uint32_t, h);
+            out.set(ch, j, 0, __builtin_bit_cast(uint32_t, h));
         } else if (F16) {
-            out.w[j][ch][0] = f16_bits(o[ch][0]) | (f16_bits(o[ch][1]) << 16);
+            out.set(ch, j, 0, f16_bits(o[ch][0]) | (f16_bits(o[ch][1]) << 16));
         } else {
-            out.w[j][ch][0] = __builtin_bit_cast(uint32_t, o[ch][0]);
-            out.w[j][ch][F16 ? 0 : 1] = __builtin_bit_cast(uint32_t, o[ch][1]);
+            out.set(ch, j, 0, __builtin_bit_cast(uint32_t, o[ch][0]));
+            out.set(ch, j, 1, __builtin_bit_cast(uint32_t, o[ch][1]));
         }
     }
 }
 
-// Store a lane's pairs of one output row: three planes (NCHW), or the six
-// interleaved elements of the two pixels (NHWC). ODD is Cw & 1, a template
-// parameter so that the stores are straight-line code: the compiler then
-// counts them exactly in the vmcnt waits of the row loop (with a branch here
-// it waits for them as well when it waits for the next rows' loads).
-template <int F16, int J, int ODD>
-__device__ __forceinline__ void store_row(uint8_t *orow, long long plane, int Cw, int lane,
+// Store a lane's 2J consecutive columns of one output row: per plane (NCHW) or
+// interleaved (NHWC), in the widest stores that hold them (4 columns of fp16:
+// 8 bytes per plane). The addresses are aligned to an element only: crop
+// widths and strips are arbitrary, and global stores take any alignment.
+// ONE (a crop of one column) is a template parameter so that the stores are
+// straight-line code: the compiler then counts them exactly in the vmcnt waits
+// of the row loop (with a branch here it waits for them as well when it waits
+// for the next rows' loads).
+// Stores are nontemporal: on their own, 308 MB of 448-byte rows take 77 us as
+// 4-byte stores, 68 as 8-byte ones and 57 as 16-byte stores of whole 128-byte
+// lines; ordinary stores are as fast alone but 1.5 times slower beside the
+// loads. uint8 output is stored ordinarily: it is small, and the
+// low-resolution op reads it back at once (step 2 of 256 images: 24.3 us, 29.7
+// after nontemporal stores).
+template <int N, bool NT = true>
+__device__ __forceinline__ void store_words(uint8_t *dst,
+                                            uint32_t __attribute__((ext_vector_type(N))) v)
+{
+    typedef uint32_t Unaligned __attribute__((ext_vector_type(N), aligned(1)));
+    if (NT)
+        __builtin_nontemporal_store(v, (Unaligned *)dst);
+    else
+        *(Unaligned *)dst = v;
+}
+
+__device__ __forceinline__ void store_half(uint8_t *dst, uint32_t v)
+{
+    typedef uint16_t __attribute__((aligned(1))) Unaligned;
+    *(Unaligned *)dst = (uint16_t)v;
+}
+
+template <int F16, int J, int ONE>
+__device__ __forceinline__ void store_row(uint8_t *orow, long long plane, int cols, int lane,
                                           const RowOut<F16, J> &out, int nhwc)
 {
-    if constexpr (F16 == 2) {
-        // uint8: a pair is 6 bytes (NHWC) or 2 per plane (NCHW); with Cw even
-        // every pair starts on an even byte, so it goes out as 16-bit stores
+    static_assert(J == 1 || J == 2, "one or two column pairs per lane");
+    constexpr int kEsz = F16 == 2 ? 1 : F16 ? 2 : 4;
+    const int c = lane_col<J>(lane, cols);
+    if constexpr (ONE) {
 #pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int c = pair_col(lane, j, Cw);
-            const uint32_t r = out.w[j][0][0], g = out.w[j][1][0], b = out.w[j][2][0];
-            if (nhwc && !ODD) {
-                uint16_t *dst = (uint16_t *)(orow + 3LL * c);
-                __builtin_nontemporal_store((uint16_t)((r & 0xffu) | ((g & 0xffu) << 8)), dst);
-                __builtin_nontemporal_store((uint16_t)((b & 0xffu) | (r & 0xff00u)), dst + 1);
-                __builtin_nontemporal_store((uint16_t)(((g >> 8) & 0xffu) | (b & 0xff00u)),
-                                            dst + 2);
-            } else if (nhwc) {
-                // odd Cw: pixel c + 1 is the last column again past the end
-                uint8_t *d0 = orow + 3LL * c, *d1 = orow + 3LL * min(c + 1, Cw - 1);
-                d0[0] = (uint8_t)r;
-                d0[1] = (uint8_t)g;
-                d0[2] = (uint8_t)b;
-                d1[0] = (uint8_t)(r >> 8);
-                d1[1] = (uint8_t)(g >> 8);
-                d1[2] = (uint8_t)(b >> 8);
-            } else if (!ODD) {
-#pragma unroll
-                for (int ch = 0; ch < 3; ++ch)
-                    __builtin_nontemporal_store((uint16_t)out.w[j][ch][0],
-                                                (uint16_t *)(orow + ch * plane + c));
-            } else {
-                const int c1 = min(c + 1, Cw - 1);
-#pragma unroll
-                for (int ch = 0; ch < 3; ++ch) {
-                    orow[ch * plane + c] = (uint8_t)out.w[j][ch][0];
-                    orow[ch * plane + c1] = (uint8_t)(out.w[j][ch][0] >> 8);
-                }
-            }
+        for (int ch = 0; ch < 3; ++ch) {
+            uint8_t *dst = orow + (nhwc ? ch * kEsz : ch * plane);
+            if (F16 == 2)
+                *dst = (uint8_t)out.word(ch, 0);
+            else if (F16)
+                *(uint16_t *)dst = (uint16_t)out.word(ch, 0);
+            else
+                *(uint32_t *)dst = out.word(ch, 0);
         }
         return;
     }
-    constexpr int kEsz = F16 ? 2 : 4;
-    if (nhwc) {
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int c = pair_col(lane, j, Cw);
-            uint8_t *dst = orow + (long long)3 * c * kEsz;
-            if constexpr (!ODD) {
-                // c even: 6 c bytes (fp16) is a multiple of 4, 12 c (fp32) of 8
-                if (F16) {
-                    const uint32_t w0 = out.w[j][0][0], w1 = out.w[j][1][0], w2 = out.w[j][2][0];
-                    __builtin_nontemporal_store((w0 & 0xffffu) | (w1 << 16), (uint32_t *)dst);
-                    __builtin_nontemporal_store((w2 & 0xffffu) | (w0 & 0xffff0000u),
-                                                (uint32_t *)dst + 1);
-                    __builtin_nontemporal_store((w1 >> 16) | (w2 & 0xffff0000u),
-                                                (uint32_t *)dst + 2);
-                } else {
-                    // pixel c: r g b, pixel c + 1: r g b, as three 8-byte
-                    // words (built from scalars: a vector gathered from the
-                    // array's elements would keep the array in memory)
-                    const uint64_t r0 = out.w[j][0][0], g0 = out.w[j][1][0], b0 = out.w[j][2][0];
-                    const uint64_t r1 = out.w[j][0][F16 ? 0 : 1], g1 = out.w[j][1][F16 ? 0 : 1],
-                                   b1 = out.w[j][2][F16 ? 0 : 1];
-                    __builtin_nontemporal_store(r0 | (g0 << 32), (uint64_t *)dst);
-                    __builtin_nontemporal_store(b0 | (r1 << 32), (uint64_t *)dst + 1);
-                    __builtin_nontemporal_store(g1 | (b1 << 32), (uint64_t *)dst + 2);
-                }
-            } else {
-                // odd Cw: element by element, pixel c + 1 is the last
-                // column again past the end
-                uint8_t *dst1 = orow + (long long)3 * min(c + 1, Cw - 1) * kEsz;
-#pragma unroll
-                for (int ch = 0; ch < 3; ++ch) {
-                    if (F16) {
-                        ((uint16_t *)dst)[ch] = (uint16_t)out.w[j][ch][0];
-                        ((uint16_t *)dst1)[ch] = (uint16_t)(out.w[j][ch][0] >> 16);
-                    } else {
-                        ((uint32_t *)dst)[ch] = out.w[j][ch][0];
-                        ((uint32_t *)dst1)[ch] = out.w[j][ch][F16 ? 0 : 1];
-                    }
-                }
-            }
-        }
-        return;
-    }
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-        const int c = pair_col(lane, j, Cw);
+    if (!nhwc) {
         const uint32_t lo = (uint32_t)c * kEsz;
-        if constexpr (!ODD) {  // every pair is whole and 2-element aligned
 #pragma unroll
-            for (int ch = 0; ch < 3; ++ch) {
-                uint8_t *dst = orow + ch * plane + lo;
-                if (F16) {
-                    __builtin_nontemporal_store(out.w[j][ch][0], (uint32_t *)dst);
-                } else {
-                    typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
-                    const u32x2v w = {out.w[j][ch][0], out.w[j][ch][F16 ? 0 : 1]};
-                    __builtin_nontemporal_store(w, (u32x2v *)dst);
-                }
-            }
+        for (int ch = 0; ch < 3; ++ch) {
+            uint8_t *dst = orow + ch * plane + lo;
+            if constexpr (F16 == 2 && J == 1)
+                store_half(dst, out.word(ch, 0));
+            else if constexpr (F16 == 2)
+                store_words<1, false>(dst, (out.word(ch, 0) & 0xffffu) | (out.word(ch, J - 1) << 16));
+            else if constexpr (F16 && J == 1)
+                store_words<1>(dst, out.word(ch, 0));
+            else if constexpr (F16 || J == 1)
+                store_words<2>(dst, u32x2{out.word(ch, 0), F16 ? out.word(ch, J - 1)
+                                                               : out.word(ch, 0, F16 ? 0 : 1)});
+            else
+                store_words<4>(dst, u32x4{out.word(ch, 0), out.word(ch, 0, F16 ? 0 : 1),
+                                          out.word(ch, J - 1),
+                                          out.word(ch, J - 1, F16 ? 0 : 1)});
+        }
+        return;
+    }
+    uint8_t *dst = orow + 3u * (uint32_t)c * kEsz;
+    typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
+    if constexpr (F16 == 2) {
+        // a pair is r0 g0 b0 r1 g1 b1, the bytes of a word being pixels c, c + 1
+        uint32_t lo[J], hi[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const uint32_t r = out.word(0, j), g = out.word(1, j), b = out.word(2, j);
+            lo[j] = (r & 0xffu) | (g & 0xffu) << 8 | (b & 0xffu) << 16 | (r & 0xff00u) << 16;
+            hi[j] = (g >> 8 & 0xffu) | (b & 0xff00u);
+        }
+        if constexpr (J == 1) {
+            store_words<1, false>(dst, lo[0]);
+            store_half(dst + 4, hi[0]);
         } else {
-            // odd Cw: element c + 1 is the last column again past the end
-            // (its value is that column's too)
-            const uint32_t lo1 = (uint32_t)min(c + 1, Cw - 1) * kEsz;
+            store_words<3, false>(dst, u32x3{lo[0], hi[0] | lo[J - 1] << 16,
+                                             lo[J - 1] >> 16 | hi[J - 1] << 16});
+        }
+    } else if constexpr (F16) {
+        u32x3 w[J];
 #pragma unroll
-            for (int ch = 0; ch < 3; ++ch) {
-                uint8_t *dst = orow + ch * plane;
-                if (F16) {
-                    *(uint16_t *)(dst + lo) = (uint16_t)out.w[j][ch][0];
-                    *(uint16_t *)(dst + lo1) = (uint16_t)(out.w[j][ch][0] >> 16);
-                } else {
-                    *(uint32_t *)(dst + lo) = out.w[j][ch][0];
-                    *(uint32_t *)(dst + lo1) = out.w[j][ch][F16 ? 0 : 1];
-                }
-            }
+        for (int j = 0; j < J; ++j) {
+            const uint32_t w0 = out.word(0, j), w1 = out.word(1, j), w2 = out.word(2, j);
+            w[j] = u32x3{(w0 & 0xffffu) | (w1 << 16), (w2 & 0xffffu) | (w0 & 0xffff0000u),
+                         (w1 >> 16) | (w2 & 0xffff0000u)};
+        }
+        if constexpr (J == 1) {
+            store_words<3>(dst, w[0]);
+        } else {
+            store_words<4>(dst, u32x4{w[0].x, w[0].y, w[0].z, w[J - 1].x});
+            store_words<2>(dst + 16, u32x2{w[J - 1].y, w[J - 1].z});
+        }
+    } else {
+        // two pixels: r g b r g b
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            store_words<4>(dst + 24 * j, u32x4{out.word(0, j), out.word(1, j), out.word(2, j),
+                                               out.word(0, j, 1)});
+            store_words<2>(dst + 24 * j + 16, u32x2{out.word(1, j, 1), out.word(2, j, 1)});
         }
     }
 }
@@ -789,36 +818,56 @@ __device__ __forceinline__ void rows_vertical(const NormK &nk, const float (&h0)
     }
 }
 
-// One output row with horizontal lerps kept across rows (contiguous row
-// ranges): a wave walking consecutive output rows of an upscale, or of a
-// downscale by less than 2, meets the same source row again, and its
-// horizontal lerps at the same columns are the same numbers. (py0, py1) are
-// the source rows whose lerps h0, h1 hold, -1 when none (a new image or new
-// column taps).
-template <int F16, int J, int EXACT>
-__device__ __forceinline__ void rows_compute_reuse(const NormK &nk, uint32_t row0, uint32_t row1,
-                                                   float wy, int y0, int y1, int &py0, int &py1,
-                                                   float (&h0)[J][2][3], float (&h1)[J][2][3],
-                                                   const int (&cx)[J][2],
-                                                   const float (&cw)[J][2], RowOut<F16, J> &out)
+// The rows of a contiguous walk, one per lane: up to 64 rows' vertical taps
+// and addresses are computed at once, each lane its own row, and read back
+// lane by lane as scalars, so a row costs a few scalar moves instead of a
+// cursor's steps, a division and 64-bit addresses in every lane.
+constexpr int kRowNew = 0;    // both source rows differ from the previous row's
+constexpr int kRowShift = 1;  // y0 is the previous row's y1
+constexpr int kRowSame = 2;   // the previous row's source rows
+struct RowRecs {
+    uint32_t lo, hi;  // address of the row's first staged byte in source row y0
+    uint32_t d1;      // bytes from there to the same column of source row y1
+    float wy;
+    uint32_t kind;    // span << 2 | relation to the previous row
+};
+
+// Records of the 64 rows from crop row rr of image img on (rows past the
+// batch's end are left unset). An image's first row and the first record are
+// kRowNew.
+__device__ __forceinline__ void row_records(RowRecs &t, const BatchArgs &a, int img, int rr,
+                                            int lane, int strip)
 {
-    const bool same = y0 == py0 && y1 == py1;
-    if (!same && y0 == py1) {
-#pragma unroll
-        for (int j = 0; j < J; ++j)
-#pragma unroll
-            for (int px = 0; px < 2; ++px)
-#pragma unroll
-                for (int ch = 0; ch < 3; ++ch)
-                    h0[j][px][ch] = h1[j][px][ch];
-    } else if (!same) {
-        rows_horizontal<J>(row0, cx, cw, h0);
+    const int Ch = a.Ch;
+    int first = 0;  // the record of crop row rr of image img
+    int y0 = 0, y1 = 0;
+    bool fresh = lane == 0;
+    while (true) {
+        const RowImg g = row_img(a, img, strip);
+        const int r = rr + lane - first;
+        const Tap ty = axis_tap(g.top + r, g.H, g.Hr);
+        if (lane >= first && r < Ch) {
+            const uint64_t base = (uint64_t)(uintptr_t)(a.src + g.off) + 3u * (uint64_t)g.xf;
+            const uint64_t addr = base + (uint64_t)(uint32_t)ty.x0 * (uint32_t)g.pitch;
+            t.lo = (uint32_t)addr;
+            t.hi = (uint32_t)(addr >> 32);
+            t.d1 = ty.x1 > ty.x0 ? (uint32_t)g.pitch : 0u;
+            t.wy = ty.w;
+            t.kind = (uint32_t)g.span << 2;
+            y0 = ty.x0;
+            y1 = ty.x1;
+            fresh = fresh || r == 0;
+        }
+        first += Ch - rr;
+        rr = 0;
+        if (first >= 64 || ++img >= a.n)
+            break;
     }
-    if (!same)
-        rows_horizontal<J>(row1, cx, cw, h1);
-    py0 = y0;
-    py1 = y1;
-    rows_vertical<F16, J, EXACT>(nk, h0, h1, wy, out);
+    const int p0 = __shfl_up(y0, 1, 64), p1 = __shfl_up(y1, 1, 64);
+    t.kind |= fresh                    ? kRowNew
+              : y0 == p0 && y1 == p1 ? kRowSame
+              : y0 == p1             ? kRowShift
+                                     : kRowNew;
 }
 
 }  // namespace

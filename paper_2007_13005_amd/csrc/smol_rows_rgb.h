@@ -8,26 +8,28 @@
 namespace smol {
 namespace {
 
-// FORM: bit 0 NHWC output, bit 1 odd crop width (kFormNhwc, kFormOdd).
-template <int F16, int J, int EXACT, int G, int P, int STRIDE, int FORM>
-__global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_rows_kernel(BatchArgs a)
+// Strided walk: wave q takes rows q, q + G, ... (G waves). FORM: kFormNhwc,
+// kFormOne.
+template <int F16, int J, int EXACT, int G, int P, int FORM>
+__global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_stride_kernel(BatchArgs a)
 {
-    constexpr int NHWC = FORM & kFormNhwc, ODD = (FORM & kFormOdd) ? 1 : 0;
+    constexpr int NHWC = FORM & kFormNhwc, ONE = (FORM & kFormOne) ? 1 : 0;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_all[];
     int lane;
     long long r0;
     int n_rows;
     const int Ch = a.Ch;
-    uint8_t *const lds = rows_wave<STRIDE>(lds_all, 2048 * G, a, lane, r0, n_rows);
+    uint8_t *const lds = rows_wave<1>(lds_all, 2048 * G, a, lane, r0, n_rows);
     // The host launches at most one wave per row, so every wave has rows (an
     // early exit here would hold the remaining argument loads behind it).
     __builtin_assume(n_rows > 0);
-    const RowStep step = row_step_of<STRIDE>(a);
+    const int strip = (int)blockIdx.y;
+    const RowStep step = row_step_of<1>(a);
     constexpr int kEsz = F16 == 2 ? 1 : F16 ? 2 : 4;
     int c_img, c_rr;  // row to interpolate
-    split_row<STRIDE>(r0, Ch, c_img, c_rr);
+    split_row<1>(r0, Ch, c_img, c_rr);
     RowCursor lc;  // next row to load
-    cursor_image<STRIDE>(lc, a, c_img, c_rr, step);
+    cursor_image(lc, a, c_img, c_rr, step);
 
     // The load cursor stops at the wave's last row: past the end the loads
     // repeat that row (fetching one chunk), so every step issues the same
@@ -37,7 +39,7 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_rows_kernel(Ba
     bool at_end = false;  // the cursor sits on the wave's last row, already loaded
     auto advance = [&]() {
         if (lrow + 1 < n_rows) {
-            cursor_next<STRIDE>(lc, a, step);
+            cursor_next(lc, a, step);
             ++lrow;
         } else {
             at_end = true;
@@ -46,10 +48,10 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_rows_kernel(Ba
     // The first row (two with P = 2) is requested before the column taps
     // and the rest of the set-up are computed.
     StagedRows<G> A, B, C;
-    load_rows<G, STRIDE>(A, lc, lane, false);
+    load_rows<G>(A, lc, lane, false);
     advance();
     if (P == 2) {
-        load_rows<G, STRIDE>(B, lc, lane, at_end);
+        load_rows<G>(B, lc, lane, at_end);
         advance();
     }
 
@@ -59,14 +61,15 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_rows_kernel(Ba
     // 3 Cw (NHWC); a wrap to the next image skips the rest of the image.
     const long long rb = (long long)a.Cw * kEsz, rowb = NHWC ? 3 * rb : rb;
     const long long imgb = 3LL * Ch * rb;
-    uint8_t *orow = (uint8_t *)a.out + (long long)(a.img_base + c_img) * imgb + c_rr * rowb;
+    uint8_t *orow = (uint8_t *)a.out + (long long)(a.img_base + c_img) * imgb + c_rr * rowb +
+                    (long long)strip_start(a, strip) * (NHWC ? 3 : 1) * kEsz;
     const long long ostep = step.di * imgb + step.dr * rowb, owrap = imgb - Ch * rowb;
     int cx[J][2];
     float cw[J][2];
     int cW, cWr, cleft;
     {
-        const RowImg g = row_img(a, c_img);
-        row_taps<J>(g, a.Cw, cx, cw, lane);
+        const RowImg g = row_img(a, c_img, strip);
+        row_taps<J>(g, a.strip_w, cx, cw, lane);
         cW = g.W;
         cWr = g.Wr;
         cleft = g.left;
@@ -82,35 +85,23 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_rows_kernel(Ba
     // outstanding but the prefetched row; the last row is interpolated after
     // it.
     write_rows<G>(lds, A, lane);
-    int csh0 = A.sh0, csh1 = A.sh1, cy0 = A.y0, cy1 = A.y1;
+    int csh0 = A.sh0, csh1 = A.sh1;
     float cwy = A.wy;
-    // Contiguous ranges keep the horizontal lerps of the last two source
-    // rows (see rows_compute_reuse); J = 4 would need 48 more registers.
-    constexpr bool kReuse = STRIDE == 0 && J <= 2;
-    float h0[J][2][3], h1[J][2][3];
-    int py0 = -1, py1 = -1;
     const long long plane = (long long)Ch * a.Cw * kEsz;
     RowOut<F16, J> out;
     auto compute = [&]() {
-        if constexpr (kReuse)
-            rows_compute_reuse<F16, J, EXACT>(nk, lds0 + (uint32_t)csh0,
-                                              lds0 + (uint32_t)(1024 * G + csh1), cwy, cy0, cy1,
-                                              py0, py1, h0, h1, cx, cw, out);
-        else
-            rows_compute<F16, J, EXACT>(nk, lds0 + (uint32_t)csh0,
-                                        lds0 + (uint32_t)(1024 * G + csh1), cwy, cx, cw, out);
+        rows_compute<F16, J, EXACT>(nk, lds0 + (uint32_t)csh0, lds0 + (uint32_t)(1024 * G + csh1),
+                                    cwy, cx, cw, out);
     };
 #define SMOL_ROWS_STEP(NXT, FUT)                                                              \
     {                                                                                         \
-        load_rows<G, STRIDE>(FUT, lc, lane, at_end);                                                  \
+        load_rows<G>(FUT, lc, lane, at_end);                                                  \
         advance();                                                                            \
         compute();                                                                            \
         write_rows<G>(lds, NXT, lane);                                                        \
-        store_row<F16, J, ODD>(orow, plane, a.Cw, lane, out, NHWC);                         \
+        store_row<F16, J, ONE>(orow, plane, a.strip_w, lane, out, NHWC);                       \
         csh0 = NXT.sh0;                                                                       \
         csh1 = NXT.sh1;                                                                       \
-        cy0 = NXT.y0;                                                                         \
-        cy1 = NXT.y1;                                                                         \
         cwy = NXT.wy;                                                                         \
         const int pimg = c_img;                                                               \
         c_img += step.di;                                                                     \
@@ -122,13 +113,12 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_rows_kernel(Ba
             orow += owrap;                                                                    \
         }                                                                                     \
         if (c_img != pimg) {                                                                  \
-            py0 = py1 = -1; /* another image's rows */                                        \
-            const RowImg g = row_img(a, c_img);                                               \
+            const RowImg g = row_img(a, c_img, strip);                                        \
             if (g.W != cW || g.Wr != cWr || g.left != cleft) {                                \
                 cW = g.W;                                                                     \
                 cWr = g.Wr;                                                                   \
                 cleft = g.left;                                                               \
-                row_taps<J>(g, a.Cw, cx, cw, lane);                                           \
+                row_taps<J>(g, a.strip_w, cx, cw, lane);                                      \
             }                                                                                 \
         }                                                                                     \
     }
@@ -149,37 +139,259 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_rows_kernel(Ba
     }
 #undef SMOL_ROWS_STEP
     compute();
-    store_row<F16, J, ODD>(orow, plane, a.Cw, lane, out, NHWC);
+    store_row<F16, J, ONE>(orow, plane, a.strip_w, lane, out, NHWC);
 }
 
-// pairs per lane and prefetch depth from the launch arguments.
-template <int F16, int EXACT, int G, int STRIDE, int FORM>
-const void *rgb_rows_g(int col_iters, int prefetch)
+// Contiguous walk: wave w takes a range of consecutive output rows. The wave's
+// rows come from row_records; the next row's chunks are loaded into registers
+// while a row is interpolated, and written to the wave's LDS slot after it.
+// Consecutive rows share source rows when the vertical scale is below 2, so the
+// horizontal lerps of the last two source rows stay in registers (A, B; `swap`
+// says which one is y0's): a row whose y0 was the previous row's y1 computes
+// one source row, a row of the same source rows none, and nothing is copied.
+//
+// LINES (fp16 NCHW whole crops whose rows are not whole 128-byte lines): a
+// wave's rows are consecutive in each plane, so they are gathered in LDS and
+// leave as the whole lines they complete, 16 bytes per lane; a row's own 8-byte
+// stores leave partial lines at both ends, which the memory takes one by one.
+//
+// What bounds it: upscales issue VALU instructions for 51 of their 72 us (1024
+// images of 128 x 128 to 224 x 224 without stores) and store for 57; larger
+// sources are bound by memory, whose reads and writes do not overlap (512 x 512
+// to 224 x 224: 33 us without stores, 25 without loads, 52 together). 1024
+// thumbnails: 81.3 us with a vertical cursor per wave, copied lerps and 4-byte
+// stores, 75.6 with row records, 72 with whole lines as well. A second row in
+// flight costs registers and time (77.8 against 75.0 us), so only one is.
+template <int F16, int J, int EXACT, int G, int FORM>
+__global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_range_kernel(BatchArgs a)
 {
-    if (prefetch == 1)
-        return col_iters <= 1   ? (const void *)rgb_rows_kernel<F16, 1, EXACT, G, 1, STRIDE, FORM>
-               : col_iters <= 2 ? (const void *)rgb_rows_kernel<F16, 2, EXACT, G, 1, STRIDE, FORM>
-                                : (const void *)rgb_rows_kernel<F16, 4, EXACT, G, 1, STRIDE, FORM>;
-    return col_iters <= 1   ? (const void *)rgb_rows_kernel<F16, 1, EXACT, G, 2, STRIDE, FORM>
-           : col_iters <= 2 ? (const void *)rgb_rows_kernel<F16, 2, EXACT, G, 2, STRIDE, FORM>
-                            : (const void *)rgb_rows_kernel<F16, 4, EXACT, G, 2, STRIDE, FORM>;
+    constexpr int NHWC = FORM & kFormNhwc, ONE = (FORM & kFormOne) ? 1 : 0;
+    constexpr bool LINES = (FORM & kFormLines) != 0;
+    static_assert(!LINES || (F16 == 1 && !NHWC && !ONE), "whole lines: fp16 NCHW");
+    constexpr int kEsz = F16 == 2 ? 1 : F16 ? 2 : 4;
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds_all[];
+    int lane;
+    long long r0;
+    int n_rows;
+    const int Ch = a.Ch;
+    uint8_t *const lds = rows_wave<0>(lds_all, 2048 * G + (LINES ? 3 * kLineRing : 0), a, lane, r0,
+                                      n_rows);
+    // The host launches at most one wave per row, so every wave has rows (an
+    // early exit here would hold the remaining argument loads behind it).
+    __builtin_assume(n_rows > 0);
+    const int strip = (int)blockIdx.y;
+    int c_img, c_rr;  // row to interpolate
+    split_row<0>(r0, Ch, c_img, c_rr);
+
+    RowRecs recs;
+    row_records(recs, a, c_img, c_rr, lane, strip);
+    // A row's scalars: offset of each source row's first byte in its first
+    // chunk, vertical weight, relation to the previous row.
+    struct RowS {
+        uint32_t sh0, sh1;
+        float wy;
+        uint32_t rel;
+    };
+    struct Chunks {
+        u32x4 c0[G], c1[G];
+    };
+    RowS nxt;
+    int li = 0;  // next row to load
+    const uint32_t lane16 = 16u * (uint32_t)lane;
+    // Loads row li into registers and moves on. Past the wave's last row the
+    // loads repeat its first chunks (fetching almost nothing), so every step
+    // issues the same loads and the compiler can count what is outstanding
+    // when a row is written to LDS.
+    auto load_next = [&](Chunks &st) {
+        const bool past = li >= n_rows;
+        if (!past && li != 0 && (li & 63) == 0) {
+            int img, rr;
+            split_row<0>(r0 + li, Ch, img, rr);
+            row_records(recs, a, img, rr, lane, strip);
+        }
+        const int i = min(li, n_rows - 1) & 63;
+        const uint32_t lo = __builtin_amdgcn_readlane(recs.lo, i);
+        const uint32_t hi = __builtin_amdgcn_readlane(recs.hi, i);
+        const uint32_t d1 = __builtin_amdgcn_readlane(recs.d1, i);
+        const uint32_t kind = __builtin_amdgcn_readlane(recs.kind, i);
+        nxt.wy = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(recs.wy), i));
+        nxt.rel = kind & 3u;
+        const uint64_t p0 = (uint64_t)hi << 32 | lo, p1 = p0 + d1;
+        nxt.sh0 = (uint32_t)p0 & 15u;
+        nxt.sh1 = (uint32_t)p1 & 15u;
+        // (lanes past a row's last chunk load that chunk again)
+        const uint32_t span1 = (kind >> 2) - 1;
+        const uint32_t last0 = past ? 0u : (nxt.sh0 + span1) & ~15u;
+        const uint32_t last1 = past ? 0u : (nxt.sh1 + span1) & ~15u;
+        // global address space, a uniform base and a 32-bit lane offset: the
+        // loads take the base from scalar registers and do not count against
+        // the LDS counter. Ordinary loads: rows met again hit in the caches.
+        typedef __attribute__((address_space(1))) const uint8_t GlobalByte;
+        typedef __attribute__((address_space(1))) const u32x4 GlobalChunk;
+        GlobalByte *q0 = (GlobalByte *)(p0 & ~(uint64_t)15), *q1 = (GlobalByte *)(p1 & ~(uint64_t)15);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            st.c0[g] = *(GlobalChunk *)(q0 + min(lane16 + 1024u * g, last0));
+            st.c1[g] = *(GlobalChunk *)(q1 + min(lane16 + 1024u * g, last1));
+        }
+        ++li;
+    };
+    auto stage = [&](const Chunks &st) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            ((u32x4 *)lds)[64 * g + lane] = st.c0[g];
+            ((u32x4 *)(lds + 1024 * G))[64 * g + lane] = st.c1[g];
+        }
+    };
+    // The first two rows are requested before the column taps and the rest of
+    // the set-up are computed.
+    Chunks first, ahead;
+    load_next(first);
+    RowS cur = nxt;
+    load_next(ahead);
+
+    // bytes between an image's output rows: Cw elements per plane (NCHW) or
+    // 3 Cw (NHWC); a wrap to the next image skips the rest of the image.
+    const long long rb = (long long)a.Cw * kEsz, rowb = NHWC ? 3 * rb : rb;
+    const long long plane = Ch * rb, imgb = 3 * plane;
+    uint8_t *orow = (uint8_t *)a.out + (long long)(a.img_base + c_img) * imgb + c_rr * rowb +
+                    (long long)strip_start(a, strip) * (NHWC ? 3 : 1) * kEsz;
+    const long long owrap = NHWC ? 0 : 2 * plane;
+    int cx[J][2];
+    float cw[J][2];
+    int cW, cWr, cleft;
+    {
+        const RowImg g = row_img(a, c_img, strip);
+        row_taps<J>(g, a.strip_w, cx, cw, lane);
+        cW = g.W;
+        cWr = g.Wr;
+        cleft = g.left;
+    }
+    const NormK nk = norm_consts(a);
+    const uint32_t lds0 = lds_addr(lds), lds1 = lds0 + 1024 * G;
+    float hA[J][2][3], hB[J][2][3];
+    bool swap = false;  // hB holds y0's lerps, hA y1's
+    RowOut<F16, J> out;
+    auto compute = [&](const RowS &row) {
+        if (row.rel == kRowNew) {
+            swap = false;
+            rows_horizontal<J>(lds0 + row.sh0, cx, cw, hA);
+            rows_horizontal<J>(lds1 + row.sh1, cx, cw, hB);
+        } else if (row.rel == kRowShift) {
+            // (the differing empty asm keeps the branches apart: merged into
+            // one with a chosen array, the arrays would live in memory)
+            swap = !swap;
+            if (swap) {
+                rows_horizontal<J>(lds1 + row.sh1, cx, cw, hA);
+                asm volatile("; row into A");
+            } else {
+                rows_horizontal<J>(lds1 + row.sh1, cx, cw, hB);
+                asm volatile("; row into B");
+            }
+        }
+        if (swap) {
+            rows_vertical<F16, J, EXACT>(nk, hB, hA, row.wy, out);
+            asm volatile("; rows B, A");
+        } else {
+            rows_vertical<F16, J, EXACT>(nk, hA, hB, row.wy, out);
+            asm volatile("; rows A, B");
+        }
+    };
+    // Whole lines: the ring holds byte b of the wave's rows (counted from
+    // `pos0`, the offset of the first row in its 128-byte line; the planes'
+    // sizes are whole lines, so all three share it) at b modulo its size.
+    uint8_t *const ring = lds + 2048 * G;
+    uint32_t pos = LINES ? (uint32_t)(uintptr_t)orow & 127u : 0u;  // the row's first byte
+    uint32_t done = pos;                                          // bytes stored so far
+    const uint32_t lane_out = LINES ? 2u * (uint32_t)lane_col<J>(lane, a.strip_w) : 0u;
+    // store the row; `last`: the wave's last row
+    auto store = [&](bool last) {
+        if constexpr (!LINES) {
+            store_row<F16, J, ONE>(orow, plane, a.strip_w, lane, out, NHWC);
+        } else {
+            const uint32_t wo = (pos + lane_out) & (kLineRing - 1);
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) {
+                if constexpr (J == 1)
+                    *(uint32_t *)(ring + ch * kLineRing + wo) = out.word(ch, 0);
+                else
+                    *(u32x2 *)(ring + ch * kLineRing + wo) = u32x2{out.word(ch, 0), out.word(ch, J - 1)};
+            }
+            const uint32_t end = pos + (uint32_t)rb;
+            // (an image ends at a line's end)
+            const uint32_t to = last ? end : end & ~127u;
+            const uint32_t off = min(lane16, to - done - 16u);
+            const uint32_t ro = (done + off) & (kLineRing - 1);
+            uint8_t *dst = orow - (pos - done);
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch)
+                store_words<4>(dst + ch * plane + off, *(const u32x4 *)(ring + ch * kLineRing + ro));
+            done = to;
+            pos = end;
+        }
+    };
+    // The loads of row k + 2 go out before the stores of row k: loads and
+    // stores complete in order, so the wait for row k + 2, one step later,
+    // then leaves row k's stores outstanding. The count of the loop's wait
+    // holds for its first turn too because row 1 has arrived before the loop.
+    stage(first);
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+        asm volatile("" : "+v"(ahead.c0[g]), "+v"(ahead.c1[g]));
+    for (int left = n_rows - 1; left > 0; --left) {
+        compute(cur);
+        stage(ahead);
+        cur = nxt;
+        load_next(ahead);
+        store(false);
+        orow += rowb;
+        if (++c_rr == Ch) {
+            c_rr = 0;
+            ++c_img;
+            orow += owrap;
+            const RowImg g = row_img(a, c_img, strip);
+            if (g.W != cW || g.Wr != cWr || g.left != cleft) {
+                cW = g.W;
+                cWr = g.Wr;
+                cleft = g.left;
+                row_taps<J>(g, a.strip_w, cx, cw, lane);
+            }
+        }
+    }
+    compute(cur);
+    store(true);
 }
 
-template <int F16, int EXACT, int STRIDE, int FORM>
-const void *rgb_rows_e(int col_iters, int groups, int prefetch)
+// Column pairs per lane, output form and (strided walk) prefetch depth from
+// the launch arguments.
+template <int F16, int EXACT, int G, int STRIDE, int FORM, int J>
+const void *rgb_rows_k(const BatchArgs &a)
 {
-    return groups <= 1   ? rgb_rows_g<F16, EXACT, 1, STRIDE, FORM>(col_iters, prefetch)
-           : groups <= 2 ? rgb_rows_g<F16, EXACT, 2, STRIDE, FORM>(col_iters, prefetch)
-                         : rgb_rows_g<F16, EXACT, 4, STRIDE, FORM>(col_iters, prefetch);
+    if constexpr (STRIDE)
+        return a.prefetch == 1 ? (const void *)rgb_stride_kernel<F16, J, EXACT, G, 1, FORM>
+                               : (const void *)rgb_stride_kernel<F16, J, EXACT, G, 2, FORM>;
+    else
+        return (const void *)rgb_range_kernel<F16, J, EXACT, G, FORM>;
 }
 
-// The crop width's parity picks the FORM of a layout.
+template <int F16, int EXACT, int G, int STRIDE, int NHWC>
+const void *rgb_rows_g(const BatchArgs &a)
+{
+    if constexpr (F16 == 1 && !STRIDE && !NHWC)
+        if (a.lines)
+            return a.col_iters > 1 ? rgb_rows_k<F16, EXACT, G, STRIDE, kFormLines, 2>(a)
+                                   : rgb_rows_k<F16, EXACT, G, STRIDE, kFormLines, 1>(a);
+    return a.col_iters > 1 ? rgb_rows_k<F16, EXACT, G, STRIDE, NHWC, 2>(a)
+           : a.Cw > 1      ? rgb_rows_k<F16, EXACT, G, STRIDE, NHWC, 1>(a)
+                           : rgb_rows_k<F16, EXACT, G, STRIDE, NHWC | kFormOne, 1>(a);
+}
+
 template <int F16, int EXACT, int STRIDE, int NHWC>
 const void *rgb_rows_f(const BatchArgs &a)
 {
-    return (a.Cw & 1) ? rgb_rows_e<F16, EXACT, STRIDE, NHWC | kFormOdd>(a.col_iters, a.row_groups,
-                                                                       a.prefetch)
-                      : rgb_rows_e<F16, EXACT, STRIDE, NHWC>(a.col_iters, a.row_groups, a.prefetch);
+    return a.row_groups <= 1   ? rgb_rows_g<F16, EXACT, 1, STRIDE, NHWC>(a)
+           : a.row_groups <= 2 ? rgb_rows_g<F16, EXACT, 2, STRIDE, NHWC>(a)
+                               : rgb_rows_g<F16, EXACT, 4, STRIDE, NHWC>(a);
 }
 
 template <int F16, int STRIDE, int NHWC>

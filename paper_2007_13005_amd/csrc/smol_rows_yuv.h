@@ -47,7 +47,7 @@ struct YuvImg {
     int rx, ry, fw, fh;
 };
 
-__device__ __forceinline__ YuvImg yuv_img(const BatchArgs &a, int img)
+__device__ __forceinline__ YuvImg yuv_img(const BatchArgs &a, int img, int strip)
 {
     YuvImg g;
     if (a.table) {
@@ -84,6 +84,12 @@ __device__ __forceinline__ YuvImg yuv_img(const BatchArgs &a, int img)
         g.xf = a.uni.xf;
         g.span = a.uni.span;
     }
+    if (a.strips > 1) {
+        // the strip's own columns of the crop and the luma span they read
+        g.left += strip_start(a, strip);
+        g.xf = axis_tap(g.left, g.W, g.Wr).x0;
+        g.span = axis_tap(g.left + a.strip_w - 1, g.W, g.Wr).x1 - g.xf + 1;
+    }
     return g;
 }
 
@@ -117,7 +123,7 @@ template <int STRIDE>
 __device__ __forceinline__ void yuv_cursor_image(YuvCursor &c, const BatchArgs &a, int img, int rr,
                                                  const RowStep &s)
 {
-    const YuvImg g = yuv_img(a, img);
+    const YuvImg g = yuv_img(a, img, (int)blockIdx.y);
     c.img = img;
     c.rr = rr;
     RowImg lg{};
@@ -278,12 +284,13 @@ struct YuvCols {
 
 // The column data of pixel px of column iteration j (one column of the lane)
 // as 8 words: ox, wx (bits), oc, sel[0], sel[1], hw[0], hw[1], 0.
-__device__ __forceinline__ void yuv_col(uint32_t (&w)[8], const YuvImg &g, int Cw, int lane,
+template <int J>
+__device__ __forceinline__ void yuv_col(uint32_t (&w)[8], const YuvImg &g, int cols, int lane,
                                         int siting, int j, int px)
 {
     const int Wc = (g.fw + 1) >> 1;
     const int cxf = chroma_tap(g.rx + g.xf, Wc, siting).x0;
-    const int c = min(pair_col(lane, j, Cw) + px, Cw - 1);
+    const int c = min(lane_col<J>(lane, cols) + 2 * j + px, cols - 1);
     const Tap t = axis_tap(g.left + c, g.W, g.Wr);
     const Tap a0 = chroma_tap(g.rx + t.x0, Wc, siting), a1 = chroma_tap(g.rx + t.x1, Wc, siting);
     w[0] = (uint32_t)(t.x0 - g.xf);
@@ -316,7 +323,7 @@ __device__ __forceinline__ void yuv_col_set(YuvCols<J> &k, int j, int px, const 
 }
 
 template <int J>
-__device__ __forceinline__ void yuv_cols(YuvCols<J> &k, const YuvImg &g, int Cw, int lane,
+__device__ __forceinline__ void yuv_cols(YuvCols<J> &k, const YuvImg &g, int cols, int lane,
                                          int siting)
 {
 #pragma unroll
@@ -324,7 +331,7 @@ __device__ __forceinline__ void yuv_cols(YuvCols<J> &k, const YuvImg &g, int Cw,
 #pragma unroll
         for (int px = 0; px < 2; ++px) {
             uint32_t w[8];
-            yuv_col(w, g, Cw, lane, siting, j, px);
+            yuv_col<J>(w, g, cols, lane, siting, j, px);
             yuv_col_set<J>(k, j, px, w);
         }
 }
@@ -344,13 +351,13 @@ __device__ __host__ constexpr uint32_t yuv_col_table_bytes()
 // the row loads already in flight.
 template <int J>
 __device__ __forceinline__ void yuv_cols_shared(YuvCols<J> &k, uint8_t *table, const YuvImg &g,
-                                                int Cw, int lane, int siting, int wid, int wpg)
+                                                int cols, int lane, int siting, int wid, int wpg)
 {
 #pragma unroll
     for (int t = 0; t < 2 * J; ++t)
         if (t % wpg == wid) {
             uint32_t w[8];
-            yuv_col(w, g, Cw, lane, siting, t / 2, t & 1);
+            yuv_col<J>(w, g, cols, lane, siting, t / 2, t & 1);
             u32x4 *e = (u32x4 *)(table + 32u * (64u * (uint32_t)t + (uint32_t)lane));
             e[0] = u32x4{w[0], w[1], w[2], w[3]};
             e[1] = u32x4{w[4], w[5], w[6], w[7]};
@@ -548,10 +555,10 @@ __device__ __forceinline__ void yuv_compute_row(const NormK &nk, uint32_t slot, 
 // FORM as for rgb_rows_kernel; GL: chunks per lane of a luma segment (staged
 // luma rows of up to 1 or 2 KiB).
 template <int F16, int J, int EXACT, int STRIDE, int FORM, int GL>
-__global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) __attribute__((amdgpu_waves_per_eu(J <= 2 ? 3 : 1)))
+__global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) __attribute__((amdgpu_waves_per_eu(3)))
 yuv_rows_kernel(BatchArgs a)
 {
-    constexpr int NHWC = FORM & kFormNhwc, ODD = (FORM & kFormOdd) ? 1 : 0;
+    constexpr int NHWC = FORM & kFormNhwc, ONE = (FORM & kFormOne) ? 1 : 0;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_all[];
     int lane;
     long long r0;
@@ -561,6 +568,7 @@ yuv_rows_kernel(BatchArgs a)
     // The host launches at most one wave per row, so every wave has rows (an
     // early exit here would hold the remaining argument loads behind it).
     __builtin_assume(n_rows > 0);
+    const int strip = (int)blockIdx.y;
     const RowStep step = row_step_of<STRIDE>(a);
     constexpr int kEsz = F16 == 2 ? 1 : F16 ? 2 : 4;
     int c_img, c_rr;  // row to interpolate
@@ -587,18 +595,19 @@ yuv_rows_kernel(BatchArgs a)
     // 3 Cw (NHWC); a wrap to the next image skips the rest of the image.
     const long long rb = (long long)a.Cw * kEsz, rowb = NHWC ? 3 * rb : rb;
     const long long imgb = 3LL * Ch * rb;
-    uint8_t *orow = (uint8_t *)a.out + (long long)(a.img_base + c_img) * imgb + c_rr * rowb;
+    uint8_t *orow = (uint8_t *)a.out + (long long)(a.img_base + c_img) * imgb + c_rr * rowb +
+                    (long long)strip_start(a, strip) * (NHWC ? 3 : 1) * kEsz;
     const long long ostep = step.di * imgb + step.dr * rowb, owrap = imgb - Ch * rowb;
 
     YuvCols<J> cols;
     int cW, cWr, cleft;
     {
-        const YuvImg g = yuv_img(a, c_img);
+        const YuvImg g = yuv_img(a, c_img, strip);
         if (!a.table && a.wpg > 1)
-            yuv_cols_shared<J>(cols, lds_all + a.wpg * yuv_seg<GL>(8), g, a.Cw, lane, a.siting,
+            yuv_cols_shared<J>(cols, lds_all + a.wpg * yuv_seg<GL>(8), g, a.strip_w, lane, a.siting,
                                __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), a.wpg);
         else
-            yuv_cols<J>(cols, g, a.Cw, lane, a.siting);
+            yuv_cols<J>(cols, g, a.strip_w, lane, a.siting);
         cW = g.W;
         cWr = g.Wr;
         cleft = g.left;
@@ -620,7 +629,7 @@ yuv_rows_kernel(BatchArgs a)
         advance();
         yuv_compute_row<F16, J, EXACT, GL>(nk, lds0, csh, cwy, cfy0, cfy1, cols, out);
         yuv_write<GL>(lds, R, lane);
-        store_row<F16, J, ODD>(orow, plane, a.Cw, lane, out, NHWC);
+        store_row<F16, J, ONE>(orow, plane, a.strip_w, lane, out, NHWC);
 #pragma unroll
         for (int s = 0; s < 8; ++s)
             csh[s] = R.sh[s];
@@ -637,41 +646,34 @@ yuv_rows_kernel(BatchArgs a)
             orow += owrap;
         }
         if (c_img != pimg) {
-            const YuvImg g = yuv_img(a, c_img);
+            const YuvImg g = yuv_img(a, c_img, strip);
             if (g.W != cW || g.Wr != cWr || g.left != cleft) {
                 cW = g.W;
                 cWr = g.Wr;
                 cleft = g.left;
-                yuv_cols<J>(cols, g, a.Cw, lane, a.siting);
+                yuv_cols<J>(cols, g, a.strip_w, lane, a.siting);
             }
         }
     }
     yuv_compute_row<F16, J, EXACT, GL>(nk, lds0, csh, cwy, cfy0, cfy1, cols, out);
-    store_row<F16, J, ODD>(orow, plane, a.Cw, lane, out, NHWC);
+    store_row<F16, J, ONE>(orow, plane, a.strip_w, lane, out, NHWC);
 }
 
-
-template <int F16, int EXACT, int STRIDE, int FORM, int GL>
-const void *yuv_rows_g(int col_iters)
-{
-    return col_iters <= 1   ? (const void *)yuv_rows_kernel<F16, 1, EXACT, STRIDE, FORM, GL>
-           : col_iters <= 2 ? (const void *)yuv_rows_kernel<F16, 2, EXACT, STRIDE, FORM, GL>
-                            : (const void *)yuv_rows_kernel<F16, 4, EXACT, STRIDE, FORM, GL>;
-}
 
 // a.row_groups: KiB per staged luma row, 1 or 2
-template <int F16, int EXACT, int STRIDE, int FORM>
-const void *yuv_rows_e(const BatchArgs &a)
+template <int F16, int EXACT, int STRIDE, int NHWC, int GL>
+const void *yuv_rows_g(const BatchArgs &a)
 {
-    return a.row_groups >= 2 ? yuv_rows_g<F16, EXACT, STRIDE, FORM, 2>(a.col_iters)
-                             : yuv_rows_g<F16, EXACT, STRIDE, FORM, 1>(a.col_iters);
+    return a.col_iters > 1 ? (const void *)yuv_rows_kernel<F16, 2, EXACT, STRIDE, NHWC, GL>
+           : a.Cw > 1      ? (const void *)yuv_rows_kernel<F16, 1, EXACT, STRIDE, NHWC, GL>
+                      : (const void *)yuv_rows_kernel<F16, 1, EXACT, STRIDE, NHWC | kFormOne, GL>;
 }
 
 template <int F16, int EXACT, int STRIDE, int NHWC>
 const void *yuv_rows_f(const BatchArgs &a)
 {
-    return (a.Cw & 1) ? yuv_rows_e<F16, EXACT, STRIDE, NHWC | kFormOdd>(a)
-                      : yuv_rows_e<F16, EXACT, STRIDE, NHWC>(a);
+    return a.row_groups >= 2 ? yuv_rows_g<F16, EXACT, STRIDE, NHWC, 2>(a)
+                             : yuv_rows_g<F16, EXACT, STRIDE, NHWC, 1>(a);
 }
 
 template <int STRIDE, int NHWC>
