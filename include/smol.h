@@ -346,12 +346,16 @@ int smol_image_geometry_ex(int32_t width, int32_t height, int32_t yuv420, const 
  *               source span plus 32 bytes is at most 4 KiB and fits the LDS
  *               budget twice, else SMOL_ERR_UNSUPPORTED; images whose 16-byte
  *               source chunks cross an end of src use the direct kernel);
- *               0: automatic (RGB: row-streaming when it fits, else
- *               register-gather when its tables fit, else LDS-staged when
- *               the span fits, else direct; I420: row-streaming when the
- *               crop is at most 512 columns, the luma span at most 2016
- *               bytes and the chroma span at most 992, else direct). For I420 only 0, 1 and 4 are
- *               valid; 4 fails with SMOL_ERR_UNSUPPORTED past those limits
+ *               0: automatic (RGB: row-streaming when it fits, in column
+ *               strips for crops up to 2048 columns or longer spans unless
+ *               lds_budget is set, else register-gather when its tables fit,
+ *               else LDS-staged when the span fits, else direct; I420:
+ *               row-streaming when the crop is at most 512 columns, the luma
+ *               span at most 2016 bytes and the chroma span at most 992, or,
+ *               for at least 64 output rows, in column strips of crops up to
+ *               2048 columns, else direct). For I420 only 0, 1 and 4 are
+ *               valid; 4 fails with SMOL_ERR_UNSUPPORTED past the limits
+ *               without strips
  *   band_rows   output rows per band in the LDS-staged kernels (1..64); for
  *               the strided walk of the row-streaming RGB kernel (row_order),
  *               1 or 2 sets how many output rows ahead of the interpolated

@@ -966,7 +966,11 @@ static int rgb_batch(const uint8_t *src, int64_t src_bytes, const int64_t *offse
                         "%lld bytes of LDS)",
                         smol::kRowsMaxCols, 1024 * smol::kRowsMaxGroups,
                         (long long)lds_bytes);
-        const bool strips_ok = rows_ok;
+        // Wider crops and longer spans run in column strips, unless the caller
+        // bounds the LDS (a strip's slot then says nothing about the row's).
+        const bool strips_ok = rows_ok || (have_dev && forced == smol::PATH_AUTO &&
+                                           g_lds_budget.load() == 0 &&
+                                           p->crop_w <= smol::kStripsMaxCols);
         int64_t strip_cols = 0;
         if (strips_ok && (forced == smol::PATH_ROWS ||
                           (forced == smol::PATH_AUTO && any_safe && runs_ok)))
@@ -1175,7 +1179,11 @@ static int yuv_batch(const uint8_t *src, int64_t src_bytes, const int64_t *y_off
     // whose planes' chunks cross an end of src go to the direct kernel.
     const bool rows_ok = p->crop_w <= smol::kRowsMaxCols && max_yspan + 32 <= 2048 &&
                          max_cspan + 32 <= 1024;
-    const bool strips_ok = rows_ok;
+    // Wider crops and longer spans run in column strips. A strip's chroma span
+    // is at most half its luma span and 2.
+    const bool strips_ok =
+        rows_ok || (forced == smol::PATH_AUTO && p->crop_w <= smol::kStripsMaxCols &&
+                    (int64_t)n * p->crop_h >= smol::kStripsMinRows);
     if (forced == smol::PATH_ROWS && !rows_ok)
         return fail(SMOL_ERR_UNSUPPORTED, "row-streaming I420 path forced but the crop is wider "
                     "than %d columns, the luma span exceeds 2016 bytes or the chroma span 992",

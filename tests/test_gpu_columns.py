@@ -1,6 +1,7 @@
 """GPU parity of the row-streaming kernels' column layout (marked gpu; run on
 an MI355X): crop widths around a lane's columns, whole-line stores and their
-remainders, walks of many rows over many images, every output type and layout.
+remainders, walks of many rows over many images, column strips of wide crops
+and of long source spans, RGB and I420, every output type and layout.
 
 Exact arithmetic is selected, so every output equals the oracle's bit for bit.
 """
@@ -47,6 +48,17 @@ def _rgb(sizes, crop, dtype, layout, seed=3):
     return _direct(wl, layout)
 
 
+def _yuv(sizes, crop, dtype, layout, siting, seed=4):
+    rng = np.random.default_rng(seed)
+    planes = [tuple(rng.integers(0, 256, size=s, dtype=np.uint8)
+                    for s in ((h, w), ((h + 1) // 2, (w + 1) // 2), ((h + 1) // 2, (w + 1) // 2)))
+              for w, h in sizes]
+    wl = synthetic.yuv420_workload("columns", planes, 1, crop, dtype)
+    wl.src = np.concatenate([wl.src, rng.integers(0, 256, 64, dtype=np.uint8)])
+    wl.siting = siting
+    return _direct(wl, layout)
+
+
 WIDTHS = [1, 2, 3, 4, 5, 63, 64, 72, 112, 127, 128, 129, 130, 131, 136, 223, 224, 255, 256]
 
 
@@ -68,3 +80,37 @@ def test_long_walks(crop, dtype):
     sizes = [(40, 30), (41, 30), (90, 64), (23, 90)]
     wl = _rgb([sizes[i % 4 if i % 7 else 0] for i in range(n)], crop, dtype, NCHW)
     assert _exact(wl, workgroups_per_cu=1)["path"] == smol.PATH_ROWS
+
+
+@pytest.mark.parametrize("width", [257, 300, 384, 385, 513, 640, 701])
+@pytest.mark.parametrize("layout", [NCHW, NHWC])
+@pytest.mark.parametrize("dtype", [F32, F16, U8])
+def test_wide_crops(width, layout, dtype):
+    sizes = [(700, 50), (333, 70)]
+    plan = _exact(_rgb(sizes, (48, width), dtype, layout))
+    assert plan["path"] == smol.PATH_ROWS
+
+
+@pytest.mark.parametrize("order", [1, 2])
+@pytest.mark.parametrize("width,crop_w", [(3840, 224), (3001, 160), (5800, 224), (5000, 640)])
+def test_long_spans(width, crop_w, order):
+    """Source spans past 4 KiB, in both row orders."""
+    wl = _rgb([(width, 60)] * 3, (40, crop_w), F16, NCHW)
+    assert _exact(wl, row_order=order)["path"] == smol.PATH_ROWS
+
+
+@pytest.mark.parametrize("siting", [smol.CHROMA_CENTER, smol.CHROMA_LEFT])
+@pytest.mark.parametrize("width,crop_w", [(300, 1), (300, 131), (2100, 224), (3840, 224),
+                                          (700, 257), (1500, 640), (4097, 301)])
+@pytest.mark.parametrize("dtype,layout", [(F32, NCHW), (F16, NCHW), (F16, NHWC)])
+def test_yuv_columns(width, crop_w, siting, dtype, layout):
+    """I420 crops and luma spans of one or more strips, a ragged batch."""
+    wl = _yuv([(width, 50), (width - 3, 41)], (40, crop_w), dtype, layout, siting)
+    assert _exact(wl)["path"] == smol.PATH_ROWS
+
+
+def test_yuv_uniform_strips():
+    """A uniform batch: the waves of a workgroup share their strip's column
+    table."""
+    wl = _yuv([(2600, 60)] * 6, (64, 250), F16, NCHW, smol.CHROMA_LEFT)
+    assert _exact(wl)["path"] == smol.PATH_ROWS
