@@ -112,25 +112,26 @@ constexpr int kRowsMaxWavesPerGroup = 4;
 // rectangle's MCU window): luma blocks 2 wmx x 2 wmy, then Cb and Cr
 // wmx x wmy, 64 each in natural order. Luma blocks lbx0 .. lbx0 + lnbx - 1
 // (rows likewise) and chroma blocks cbx0 .. are decoded; jobs_end counts the
-// kernel's jobs (groups of up to eight blocks along a block row) of this and
-// the earlier runs.
+// kernel's jobs of this and the earlier runs.
 constexpr int kJpegMaxRuns = 24;
 constexpr int kJpegMaxTables = 8;
+// Blocks of a job: those of a block row's rectangle in this many adjacent ones,
+// aligned to as many in the plane (the kernel's sixteen).
+constexpr int kJpegJobBlocks = 16;
 struct JpegRun {
     long long coef, coef_stride, out, out_stride, cboff, croff;
     int32_t W, H;
     int16_t wx0, wy0, wmx, wmy;
     int16_t lbx0, lby0, lnbx, lnby, cbx0, cby0, cnbx, cnby;
-    // Jobs of a frame: lum = lg * lnby luma groups (lg groups of up to eight
-    // blocks per block row), then chr = cg * cnby groups of each chroma
-    // plane; a row's last group holds lrem (cg: crem) blocks.
+    // Jobs of a frame: lum = lg * lnby luma jobs (lg per block row), then
+    // chr = cg * cnby jobs of each chroma plane.
     uint32_t lum, chr;
     uint32_t jobs_end;  // < 2^31
     // Division by a divisor d of the run (jobs per frame, lg, cg) as
     // floor(n m / 2^s) with m = ceil(2^s / d), s = 31 + ceil(log2 d): exact
     // for every n < 2^31.
     uint32_t m_pf, m_lg, m_cg;
-    uint32_t groups;  // lg | cg << 11 | lrem << 22 | crem << 26
+    uint32_t jobs_row;  // lg | cg << 16
     uint32_t shifts;  // s of the frame's jobs | s of lg << 8 | s of cg << 16 | qt << 24
 };
 struct JpegArgs {
@@ -138,7 +139,7 @@ struct JpegArgs {
     uint8_t *out;
     int32_t runs, pad;
     uint8_t q[kJpegMaxTables][2][64];  // luma, chroma dequantisation (entries 1..255)
-    float c[64];                       // c[k * 8 + n] = fp32(C(k)/2 cos((2n + 1) k pi / 16))
+    float c[8];                        // c[k] = fp32(C(k)/2 cos(k pi / 16))
     JpegRun run[kJpegMaxRuns];
 };
 static_assert(sizeof(JpegRun) == 112, "run table entry of block decoding");

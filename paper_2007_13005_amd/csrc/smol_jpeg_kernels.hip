@@ -3,17 +3,31 @@
 // 4:2:0 frame that meet a rectangle, written to I420 planes. The entropy
 // decoding that produces the coefficients is the CPU decoder's.
 //
-// A wave decodes up to eight horizontally adjacent blocks of one block row
-// at a time. Each 1-D transform x(n) = sum_k c(k, n) D(k) is evaluated
-// through the parity of the cosine basis, c(k, 7 - n) = (-1)^k c(k, n): for
-// n < 4 the even-frequency sum E and the odd-frequency sum O (each in
-// increasing frequency), then x(n) = E + O and x(7 - n) = E - O (T.81 A.3.3
-// evaluated separably), each product and sum rounded on its own (no
-// contraction). Pass 1: lane l loads coefficient row v = l % 8 of block
-// b = l / 8 (16 contiguous bytes) and forms G(v, x) for all x in registers.
-// After an exchange through LDS, pass 2: lane l forms output rows y and 7 - y
-// (y = l % 4) of block b at columns 4 h .. 4 h + 3 (h = (l % 8) / 4). Then
-// + 128, clamped to [0, 255] and rounded to nearest even.
+// Each 1-D transform x(n) = sum_k c(k, n) D(k) is evaluated through the parity
+// of the cosine basis, c(k, 7 - n) = (-1)^k c(k, n): for n < 4 the
+// even-frequency sum E and the odd-frequency sum O (each in increasing
+// frequency), then x(n) = E + O and x(7 - n) = E - O (T.81 A.3.3 evaluated
+// separably), each product and sum rounded on its own (no contraction). Every
+// c(k, n) is one of seven magnitudes with a sign (c(2, 3) = -c(2, 0), and so
+// on), so the even frequencies need 6 products for the four E instead of 16:
+// the products are the same numbers up to an exact negation.
+//
+// A job is the rectangle's blocks among sixteen adjacent ones of a block row
+// (aligned to sixteen in the plane), decoded by one wave in two halves of
+// eight. Pass 1: lane l loads coefficient row v = l % 8
+// of block b = l / 8 (16 contiguous bytes) and forms G(v, x) for all x. After an
+// exchange through LDS, pass 2: lane l forms column x = l % 8 of block b, adds
+// 128, clamps to [0, 255] and rounds to nearest even. The bytes of the sixteen
+// blocks go through LDS once more, so that a lane stores 16 bytes of a picture
+// row and eight lanes 128, a whole line of the plane where its rows are.
+//
+// Bound by memory: the rectangles of 128 720p frames are 157 MB of coefficients
+// and 81 MB of pixels, 47 us at a large copy's 5.05 TB/s. 59.5 us with one
+// group of eight per job, 4-byte stores of 64-byte row pieces and every
+// output's products formed on their own (194 vector and 110 scalar instructions
+// per group), 48 us now (about 155 and 45); with nontemporal coefficient loads
+// the planes stay cached for the preprocessing that reads them next (2 us of
+// the pair of launches; nontemporal stores cost it 1.5).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -23,7 +37,27 @@ namespace smol {
 namespace {
 
 constexpr int kBlocksPerWave = 8;
-constexpr int kBlockWords = 68;
+// LDS words of a block's G: eight more than its 64, so that the columns of the
+// eight blocks read together (pass 2) lie in different banks.
+constexpr int kBlockWords = 72;
+
+// x = the 1-D transform of d; c[k] = C(k)/2 cos(k pi / 16).
+__device__ __forceinline__ void idct8(const float (&c)[8], const float (&d)[8], float (&x)[8])
+{
+    const float p0 = c[0] * d[0], p4 = c[4] * d[4];
+    const float a2 = c[2] * d[2], b2 = c[6] * d[2], a6 = c[6] * d[6], b6 = c[2] * d[6];
+    const float e[4] = {((p0 + a2) + p4) + a6, ((p0 + b2) - p4) - b6, ((p0 - b2) - p4) + b6,
+                        ((p0 - a2) + p4) - a6};
+    const float o[4] = {((c[1] * d[1] + c[3] * d[3]) + c[5] * d[5]) + c[7] * d[7],
+                        ((c[3] * d[1] - c[7] * d[3]) - c[1] * d[5]) - c[5] * d[7],
+                        ((c[5] * d[1] - c[1] * d[3]) + c[7] * d[5]) + c[3] * d[7],
+                        ((c[7] * d[1] - c[5] * d[3]) + c[3] * d[5]) - c[1] * d[7]};
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+        x[n] = e[n] + o[n];
+        x[7 - n] = e[n] - o[n];
+    }
+}
 
 // The 32-bit word at a 4-byte aligned field, and its two 16-bit halves.
 __device__ __forceinline__ uint32_t word_of(const int16_t *p)
@@ -43,17 +77,16 @@ __device__ __forceinline__ uint32_t magic_div(uint32_t n, uint32_t m, uint32_t s
 
 __global__ void __launch_bounds__(64) jpeg_idct_kernel(JpegArgs a)
 {
-    // G(v, x) of block b at word b * kBlockWords + 8 v + x: the 4-word pad
-    // per block spreads the eight blocks' rows over the LDS banks (with 64
-    // words per block every block's row v sits in the same banks)
+    // G(v, x) of block b at word b * kBlockWords + 8 v + x; pixel (y, x) of the
+    // sixteen blocks' 8 x 128 at byte 128 y + x
     __shared__ __attribute__((aligned(16))) float g[kBlocksPerWave * kBlockWords];
+    __shared__ __attribute__((aligned(16))) uint8_t pix[2 * kBlocksPerWave * 64];
     const int l = threadIdx.x;
-    const int b = l >> 3, row = l & 7;  // block of the group; coefficient row v of pass 1
-    const int y = row & 3, h = row >> 2;  // pass 2: output rows y, 7 - y; columns 4h .. 4h + 3
-    float cy[8];                          // c(k, y) for pass 2
+    const int b = l >> 3, row = l & 7;  // block of the group; row v (pass 1), column x (pass 2)
+    float c[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k)
-        cy[k] = a.c[k * 8 + y];
+        c[k] = a.c[k];
     // job indices stay below 2^31 (the host splits launches), so the job
     // mapping runs in 32-bit unsigned arithmetic, its divisions by the run's
     // divisors as multiplications (JpegRun)
@@ -63,8 +96,8 @@ __global__ void __launch_bounds__(64) jpeg_idct_kernel(JpegArgs a)
         while (a.run[ri].jobs_end <= job)
             ++ri;
         const JpegRun &r = a.run[ri];
-        // groups of up to eight blocks along each block row of the rectangle
-        const uint32_t lg = r.groups & 0x7ffu, cg = (r.groups >> 11) & 0x7ffu;
+        // jobs along each block row of the rectangle
+        const uint32_t lg = r.jobs_row & 0xffffu, cg = r.jobs_row >> 16;
         const uint32_t lum = r.lum, chr = r.chr, per_frame = lum + 2 * chr;
         const uint32_t local = job - (ri ? a.run[ri - 1].jobs_end : 0);
         const uint32_t f = magic_div(local, r.m_pf, r.shifts & 0xffu);
@@ -72,16 +105,16 @@ __global__ void __launch_bounds__(64) jpeg_idct_kernel(JpegArgs a)
         // the 16-bit fields in pairs, as the words that hold them (a 16-bit
         // field read alone becomes a vector load that the wave waits for)
         const uint32_t wxy = word_of(&r.wx0), wm = word_of(&r.wmx);
-        int comp, by, bx0, nb, gw, ox, oy, pw, ph;  // (ox, oy): the stored grid's first block
+        int comp, by, bx0, nbx, gi, gw, ox, oy, pw, ph;  // (ox, oy): the stored grid's first block
         long long cbase, pbase;
         if (k < lum) {
             comp = 0;
             const uint32_t kr = magic_div(k, r.m_lg, (r.shifts >> 8) & 0xffu);
             const uint32_t lb = word_of(&r.lbx0);
             by = hi16(lb) + (int)kr;
-            const uint32_t gi = k - kr * lg;
-            bx0 = lo16(lb) + (int)gi * kBlocksPerWave;
-            nb = gi + 1 == lg ? (int)((r.groups >> 22) & 0xfu) : kBlocksPerWave;
+            gi = (int)(k - kr * lg);
+            bx0 = lo16(lb);
+            nbx = lo16(word_of(&r.lnbx));
             gw = 2 * lo16(wm);
             ox = 2 * lo16(wxy);
             oy = 2 * hi16(wxy);
@@ -96,9 +129,9 @@ __global__ void __launch_bounds__(64) jpeg_idct_kernel(JpegArgs a)
             const uint32_t kr = magic_div(k, r.m_cg, (r.shifts >> 16) & 0xffu);
             const uint32_t cb = word_of(&r.cbx0);
             by = hi16(cb) + (int)kr;
-            const uint32_t gi = k - kr * cg;
-            bx0 = lo16(cb) + (int)gi * kBlocksPerWave;
-            nb = gi + 1 == cg ? (int)(r.groups >> 26) : kBlocksPerWave;
+            gi = (int)(k - kr * cg);
+            bx0 = lo16(cb);
+            nbx = lo16(word_of(&r.cnbx));
             gw = lo16(wm);
             ox = lo16(wxy);
             oy = hi16(wxy);
@@ -107,78 +140,64 @@ __global__ void __launch_bounds__(64) jpeg_idct_kernel(JpegArgs a)
             pw = (r.W + 1) >> 1;
             ph = (r.H + 1) >> 1;
         }
-        // lanes of blocks past the group's end repeat its last block
-        const int bb = min(b, nb - 1);
-        const int16_t *blk = a.coef + r.coef + f * r.coef_stride + cbase +
-                             64LL * ((long long)(by - oy) * gw + bx0 + bb - ox);
+        // the job's blocks: begin .. end - 1 of the plane's block row
+        const int first = (bx0 / kJpegJobBlocks + gi) * kJpegJobBlocks;
+        const int begin = max(bx0, first), end = min(bx0 + nbx, first + kJpegJobBlocks);
+        const int16_t *blocks = a.coef + r.coef + f * r.coef_stride + cbase +
+                                64LL * ((long long)(by - oy) * gw - ox);
+        // the lane's 8 table entries
+        const uint64_t q = *(const uint64_t *)&a.q[r.shifts >> 24][comp == 0 ? 0 : 1][8 * row];
+        uint8_t *const plane = a.out + r.out + f * r.out_stride + pbase;
         typedef short short8 __attribute__((ext_vector_type(8)));
-        const short8 raw = *(const short8 *)(blk + 8 * row);
-        const uint8_t *q = a.q[r.shifts >> 24][comp == 0 ? 0 : 1];
-        float d[8];
+        // coefficient row of the lane's block in the eight from block b0 on;
+        // lanes of blocks outside the job repeat one inside
+        auto load = [&](int b0) {
+            const short8 *p = (const short8 *)(
+                blocks + (uint32_t)(64 * min(max(b0 + b, begin), end - 1) + 8 * row));
+            return __builtin_nontemporal_load(p);  // read once: keeps the planes cached
+        };
+        const short8 raw[2] = {load(first), load(first + kBlocksPerWave)};
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-            d[u] = (float)((int)raw[u] * (int)q[8 * row + u]);  // exact: |.| < 2^24
-        // horizontal pass for row v = row of block bb: x = 0..3 and 7..4,
-        // written as two 16-byte stores
-        typedef float f32x4 __attribute__((ext_vector_type(4)));
-        f32x4 lo, hi;
+        for (int h = 0; h < 2; ++h) {
+            const int b0 = first + h * kBlocksPerWave;
+            if (b0 + kBlocksPerWave <= begin || b0 >= end)
+                continue;  // none of these eight is in the job
+            float d[8], x[8];
 #pragma unroll
-        for (int n = 0; n < 4; ++n) {
-            float e = a.c[0 * 8 + n] * d[0];
-            e = e + a.c[2 * 8 + n] * d[2];
-            e = e + a.c[4 * 8 + n] * d[4];
-            e = e + a.c[6 * 8 + n] * d[6];
-            float o = a.c[1 * 8 + n] * d[1];
-            o = o + a.c[3 * 8 + n] * d[3];
-            o = o + a.c[5 * 8 + n] * d[5];
-            o = o + a.c[7 * 8 + n] * d[7];
-            lo[n] = e + o;
-            hi[3 - n] = e - o;
+            for (int u = 0; u < 8; ++u)
+                d[u] = (float)((int)raw[h][u] * (int)(uint8_t)(q >> (8 * u)));  // exact: < 2^24
+            // horizontal pass for row v = row
+            idct8(c, d, x);
+            typedef float f32x4 __attribute__((ext_vector_type(4)));
+            f32x4 *grow = (f32x4 *)&g[b * kBlockWords + 8 * row];
+            grow[0] = f32x4{x[0], x[1], x[2], x[3]};
+            grow[1] = f32x4{x[4], x[5], x[6], x[7]};
+            __syncthreads();
+            // vertical pass for column x = row
+#pragma unroll
+            for (int v = 0; v < 8; ++v)
+                d[v] = g[b * kBlockWords + 8 * v + row];
+            idct8(c, d, x);
+#pragma unroll
+            for (int y = 0; y < 8; ++y)
+                // clamped to [0, 255] and rounded to nearest even
+                pix[128 * y + 64 * h + l] =
+                    (uint8_t)__builtin_amdgcn_cvt_pk_u8_f32(x[y] + 128.0f, 0u, 0u);
+            __syncthreads();
         }
-        f32x4 *grow = (f32x4 *)&g[b * kBlockWords + 8 * row];
-        grow[0] = lo;
-        grow[1] = hi;
-        __syncthreads();
-        // vertical pass: rows y and 7 - y of block bb at columns 4h .. 4h + 3
-        f32x4 gv[8];
-#pragma unroll
-        for (int v = 0; v < 8; ++v)
-            gv[v] = *(const f32x4 *)&g[b * kBlockWords + 8 * v + 4 * h];
-        uint32_t top = 0, bot = 0;  // four pixels of row y, four of row 7 - y
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float e = cy[0] * gv[0][i];
-            e = e + cy[2] * gv[2][i];
-            e = e + cy[4] * gv[4][i];
-            e = e + cy[6] * gv[6][i];
-            float o = cy[1] * gv[1][i];
-            o = o + cy[3] * gv[3][i];
-            o = o + cy[5] * gv[5][i];
-            o = o + cy[7] * gv[7][i];
-            // v_cvt_pk_u8_f32: byte i = the value clamped to [0, 255] and
-            // rounded to nearest even (one instruction for clamp, round,
-            // convert and insert)
-            top = __builtin_amdgcn_cvt_pk_u8_f32((e + o) + 128.0f, (uint32_t)i, top);
-            bot = __builtin_amdgcn_cvt_pk_u8_f32((e - o) + 128.0f, (uint32_t)i, bot);
-        }
-        const int gx = 8 * (bx0 + b) + 4 * h;
-        if (b < nb && gx < pw) {
-            uint8_t *base = a.out + r.out + f * r.out_stride + pbase;
-            const int gy[2] = {8 * by + y, 8 * by + 7 - y};
-            const uint32_t pix[2] = {top, bot};
-#pragma unroll
-            for (int k = 0; k < 2; ++k) {
-                if (gy[k] >= ph)
-                    continue;
-                uint8_t *dst = base + (long long)gy[k] * pw + gx;
-                if (gx + 4 <= pw && ((uintptr_t)dst & 3) == 0) {
-                    *(uint32_t *)dst = pix[k];
-                } else {
-#pragma unroll
-                    for (int x = 0; x < 4; ++x)
-                        if (gx + x < pw)
-                            dst[x] = (uint8_t)(pix[k] >> (8 * x));
-                }
+        // lane l stores 16 bytes of row l / 8 of the sixteen blocks
+        const int gx = 8 * first + 16 * row, gy = 8 * by + b;
+        const int x_end = min(8 * end, pw);
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        const u32x4 px = *(const u32x4 *)&pix[16 * l];
+        if (gy < ph) {
+            uint8_t *dst = plane + (uint32_t)gy * (uint32_t)pw;
+            if (gx >= 8 * begin && gx + 16 <= x_end) {
+                typedef uint32_t Unaligned __attribute__((ext_vector_type(4), aligned(1)));
+                *(Unaligned *)(dst + (uint32_t)gx) = px;
+            } else {
+                for (int x = max(gx, 8 * begin); x < min(gx + 16, x_end); ++x)
+                    dst[x] = pix[16 * l + x - gx];
             }
         }
         __syncthreads();

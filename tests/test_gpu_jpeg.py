@@ -103,6 +103,20 @@ def test_ragged_batch_spans_several_launches():
     note(f"    {wl.n} frames in {runs} runs decoded bit for bit")
 
 
+@pytest.mark.parametrize("width", [129, 300, 391])
+def test_rectangles_around_a_waves_blocks(width):
+    """Rectangles that begin and end at every block around a wave's sixteen
+    (128 pixels), in frames whose rows start at any byte."""
+    xs = [0, 2, 8, 56, 62, 64, 118, 126, 128]
+    rects = [(x, 2, w, 30) for x in xs for w in (1, 8, 17, 64, 129, 272) if x + w <= width]
+    wl = synthetic.jpeg_workload("jpeg-edges", [(width, 37)] * len(rects), 16, 8, F16, 57)
+    got = _gpu_decode(wl, rects, fill=7)
+    for i, r in enumerate(rects):
+        exp = _oracle_decode(wl, i, r, fill=7)
+        for k in range(3):
+            assert np.array_equal(got[i][k], exp[k]), (r, k)
+
+
 @pytest.mark.parametrize("layout", [smol.LAYOUT_NCHW, smol.LAYOUT_NHWC])
 @pytest.mark.parametrize("dtype", [F32, F16])
 def test_partial_decode_then_preprocess(dtype, layout):
