@@ -9,6 +9,7 @@ import re
 import shutil
 import subprocess
 import sys
+import sysconfig
 import tempfile
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -16,6 +17,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libsmol.so")
+PYCALL = os.path.join(PKG, "_smolcall.so")  # the binding's native marshalling
 
 # The row-streaming kernels are split into parts (input, output type, row
 # walk, output layout) so that the compiler runs on the parts in parallel.
@@ -110,8 +112,24 @@ def _scratch_users(stderr: str) -> list:
     return users
 
 
+def build_pycall(verbose: bool = False) -> str:
+    """The CPython extension of the binding (host code only)."""
+    cc = shutil.which("gcc") or shutil.which("cc") or hipcc()
+    tmp = PYCALL + ".tmp"
+    cmd = [cc, "-O2", "-Wall", "-shared", "-fPIC", "-I", sysconfig.get_paths()["include"], "-o",
+           tmp, os.path.join(CSRC, "smol_pycall.c")]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"building _smolcall failed ({res.returncode}):\n{res.stderr}")
+    os.replace(tmp, PYCALL)
+    return PYCALL
+
+
 def build(verbose: bool = False) -> str:
     cc = hipcc()
+    build_pycall(verbose)
     tmp = LIB + ".tmp"
     with tempfile.TemporaryDirectory(prefix="smol_build_") as objdir:
         cmds = []
@@ -153,10 +171,10 @@ def build(verbose: bool = False) -> str:
 
 
 def sources_newer_than_lib() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(PYCALL):
         return True
-    t = os.path.getmtime(LIB)
-    files = [os.path.join(CSRC, f) for f in SOURCES + HEADERS] + [
+    t = min(os.path.getmtime(LIB), os.path.getmtime(PYCALL))
+    files = [os.path.join(CSRC, f) for f in SOURCES + HEADERS + ["smol_pycall.c"]] + [
         os.path.join(INCLUDE, f) for f in os.listdir(INCLUDE) if f.endswith(".h")]
     return any(os.path.getmtime(f) > t for f in files)
 

@@ -8,6 +8,7 @@ fallback.
 from __future__ import annotations
 
 import ctypes
+import operator
 import os
 import sys
 import threading
@@ -189,6 +190,9 @@ SIGNATURES = {
 }
 
 _lib = None
+_torch = None
+_smolcall = None
+_addresses: dict = {}  # of the loaded library's functions
 
 
 class SmolError(RuntimeError):
@@ -208,7 +212,7 @@ def lib() -> ctypes.CDLL:
     # torch ships its own HIP runtime with the same soname (libamdhip64.so.7).
     # Loading torch first makes libsmol bind to that runtime, so that torch's
     # device pointers and streams and libsmol's launches share one runtime.
-    import torch  # noqa: F401
+    _load_modules()
     handle = ctypes.CDLL(LIB_PATH)
     runtimes = _mapped_hip_runtimes()
     if len(runtimes) > 1:
@@ -216,6 +220,29 @@ def lib() -> ctypes.CDLL:
     bind_signatures(handle)
     _lib = handle
     return handle
+
+
+def _load_modules() -> None:
+    global _torch, _smolcall
+    if _smolcall is None:
+        import torch
+        try:
+            from . import _smolcall as native
+        except ImportError as e:
+            raise RuntimeError("the _smolcall extension is missing: build it with "
+                               "`python -m paper_2007_13005_amd.build`") from e
+        _torch, _smolcall = torch, native
+
+
+def _call(name: str, *args) -> None:
+    """Call an ABI function through the native marshalling: integers, None,
+    and objects with a contiguous buffer (arrays, structures), whose address
+    is passed. Raises on an error status."""
+    handle = lib()
+    address = _addresses.get(name)
+    if address is None:
+        address = _addresses[name] = ctypes.cast(getattr(handle, name), ctypes.c_void_p).value
+    _check(_smolcall.call(address, *args))
 
 
 def bind_signatures(handle: ctypes.CDLL, required: bool = True) -> ctypes.CDLL:
@@ -363,8 +390,12 @@ def _launch_stream(stream, *tensors) -> int:
     waits for the current stream's work (which made or filled the tensors),
     and the device tensors are recorded on it so that torch's allocator does
     not hand their memory out again before the call's work has finished."""
-    import torch
+    _load_modules()
+    torch = _torch
     if stream is None:
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:  # the same handle without making a Stream object
+            return raw(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     st = torch.cuda.ExternalStream(stream) if isinstance(stream, int) else stream
     cur = torch.cuda.current_stream()
@@ -377,13 +408,16 @@ def _launch_stream(stream, *tensors) -> int:
 
 
 def _out_tensor(out, n: int, params: Params, device, layout: int = LAYOUT_NCHW):
-    import torch
-    dtype = {OUT_F16: torch.float16, OUT_U8: torch.uint8}.get(params.out_dtype, torch.float32)
+    _load_modules()
+    torch = _torch
+    kind = params.out_dtype
+    dtype = (torch.float16 if kind == OUT_F16 else torch.uint8 if kind == OUT_U8
+             else torch.float32)
     shape = ((n, params.crop_h, params.crop_w, 3) if layout == LAYOUT_NHWC
              else (n, 3, params.crop_h, params.crop_w))
     if out is None:
         return torch.empty(shape, dtype=dtype, device=device)
-    if tuple(out.shape) != shape or out.dtype != dtype or not out.is_contiguous():
+    if out.shape != shape or out.dtype != dtype or not out.is_contiguous():
         raise ValueError(f"out must be a contiguous {dtype} tensor of shape {shape}")
     return out
 
@@ -418,17 +452,11 @@ def preprocess_batch(src, offsets, widths, heights, params: Params, pitches=None
     r = _rois(rois, n)
     out = _out_tensor(out, n, params, src.device, options.layout if options else LAYOUT_NCHW)
     if r is None and options is None:
-        _check(lib().smol_preprocess_batch(src.data_ptr(), src.numel(), off.ctypes.data,
-                                           w.ctypes.data, h.ctypes.data,
-                                           None if pt is None else pt.ctypes.data, n,
-                                           ctypes.byref(params), out.data_ptr(),
-                                           _launch_stream(stream, src, out)))
+        _call("smol_preprocess_batch", src.data_ptr(), src.numel(), off, w, h, pt, n, params,
+              out.data_ptr(), _launch_stream(stream, src, out))
     else:
-        _check(lib().smol_preprocess_batch_ex(
-            src.data_ptr(), src.numel(), off.ctypes.data, w.ctypes.data, h.ctypes.data,
-            None if pt is None else pt.ctypes.data, None if r is None else r.ctypes.data, n,
-            ctypes.byref(params), None if options is None else ctypes.byref(options),
-            out.data_ptr(), _launch_stream(stream, src, out)))
+        _call("smol_preprocess_batch_ex", src.data_ptr(), src.numel(), off, w, h, pt, r, n,
+              params, options, out.data_ptr(), _launch_stream(stream, src, out))
     return out
 
 
@@ -450,17 +478,11 @@ def yuv420_preprocess_batch(src, y_offsets, cb_offsets, cr_offsets, widths, heig
     r = _rois(rois, n)
     out = _out_tensor(out, n, params, src.device, options.layout if options else LAYOUT_NCHW)
     if r is None and options is None:
-        _check(lib().smol_yuv420_preprocess_batch(src.data_ptr(), src.numel(), yo.ctypes.data,
-                                                  bo.ctypes.data, ro.ctypes.data, w.ctypes.data,
-                                                  h.ctypes.data, n, ctypes.byref(params),
-                                                  out.data_ptr(),
-                                                  _launch_stream(stream, src, out)))
+        _call("smol_yuv420_preprocess_batch", src.data_ptr(), src.numel(), yo, bo, ro, w, h, n,
+              params, out.data_ptr(), _launch_stream(stream, src, out))
     else:
-        _check(lib().smol_yuv420_preprocess_batch_ex(
-            src.data_ptr(), src.numel(), yo.ctypes.data, bo.ctypes.data, ro.ctypes.data,
-            w.ctypes.data, h.ctypes.data, None if r is None else r.ctypes.data, n,
-            ctypes.byref(params), None if options is None else ctypes.byref(options),
-            out.data_ptr(), _launch_stream(stream, src, out)))
+        _call("smol_yuv420_preprocess_batch_ex", src.data_ptr(), src.numel(), yo, bo, ro, w, h,
+              r, n, params, options, out.data_ptr(), _launch_stream(stream, src, out))
     return out
 
 
@@ -495,10 +517,9 @@ def lowres_preprocess_batch(src, offsets, widths, heights, params: Params, low_r
         raise ValueError("table lengths differ")
     out = _out_tensor(out, n, params, src.device)
     ws = _workspace(workspace, n, low_res, src.device)
-    _check(lib().smol_lowres_preprocess_batch(
-        src.data_ptr(), src.numel(), off.ctypes.data, w.ctypes.data, h.ctypes.data,
-        None if pt is None else pt.ctypes.data, n, low_res, ctypes.byref(params), ws.data_ptr(),
-        ws.numel(), out.data_ptr(), _launch_stream(stream, src, out, ws)))
+    _call("smol_lowres_preprocess_batch", src.data_ptr(), src.numel(), off, w, h, pt, n,
+          operator.index(low_res), params, ws.data_ptr(), ws.numel(), out.data_ptr(),
+          _launch_stream(stream, src, out, ws))
     return out
 
 
@@ -518,10 +539,9 @@ def yuv420_lowres_preprocess_batch(src, y_offsets, cb_offsets, cr_offsets, width
         raise ValueError("table lengths differ")
     out = _out_tensor(out, n, params, src.device)
     ws = _workspace(workspace, n, low_res, src.device)
-    _check(lib().smol_yuv420_lowres_preprocess_batch(
-        src.data_ptr(), src.numel(), yo.ctypes.data, bo.ctypes.data, ro.ctypes.data,
-        w.ctypes.data, h.ctypes.data, n, low_res, ctypes.byref(params), ws.data_ptr(),
-        ws.numel(), out.data_ptr(), _launch_stream(stream, src, out, ws)))
+    _call("smol_yuv420_lowres_preprocess_batch", src.data_ptr(), src.numel(), yo, bo, ro, w, h,
+          n, operator.index(low_res), params, ws.data_ptr(), ws.numel(), out.data_ptr(),
+          _launch_stream(stream, src, out, ws))
     return out
 
 
@@ -572,11 +592,9 @@ def jpeg_decode_i420(coef, coef_offsets, qtables, widths, heights, out, y_offset
     n = len(co)
     r = None if rects is None else _rois(rects, n)
     q, nq = _qtables(qtables, n)
-    _check(lib().smol_jpeg_decode_i420(
-        coef.data_ptr(), coef.numel(), co.ctypes.data, q.ctypes.data, nq, w.ctypes.data,
-        h.ctypes.data, None if r is None else r.ctypes.data, n, coef_layout, out.data_ptr(),
-        out.numel(), yo.ctypes.data, bo.ctypes.data, ro.ctypes.data,
-        _launch_stream(stream, coef, out)))
+    _call("smol_jpeg_decode_i420", coef.data_ptr(), coef.numel(), co, q, nq, w, h, r, n,
+          operator.index(coef_layout), out.data_ptr(), out.numel(), yo, bo, ro,
+          _launch_stream(stream, coef, out))
 
 
 def jpeg_workspace_bytes(widths, heights) -> int:
@@ -600,11 +618,9 @@ def jpeg_roi_preprocess_batch(coef, coef_offsets, qtables, widths, heights, para
     if workspace is None:
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=coef.device)
     out = _out_tensor(out, n, params, coef.device, options.layout if options else LAYOUT_NCHW)
-    _check(lib().smol_jpeg_roi_preprocess_batch(
-        coef.data_ptr(), coef.numel(), co.ctypes.data, q.ctypes.data, nq, w.ctypes.data,
-        h.ctypes.data, n, coef_layout, ctypes.byref(params),
-        None if options is None else ctypes.byref(options), workspace.data_ptr(),
-        workspace.numel(), out.data_ptr(), _launch_stream(stream, coef, out, workspace)))
+    _call("smol_jpeg_roi_preprocess_batch", coef.data_ptr(), coef.numel(), co, q, nq, w, h, n,
+          operator.index(coef_layout), params, options, workspace.data_ptr(), workspace.numel(),
+          out.data_ptr(), _launch_stream(stream, coef, out, workspace))
     return out
 
 
