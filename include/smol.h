@@ -377,11 +377,11 @@ int smol_image_geometry_ex(int32_t width, int32_t height, int32_t yuv420, const 
  *               one fp32 ulp from the quotient, and may round that product
  *               to fp16 directly (within one fp16 ulp). Every interpolation
  *               and colour-conversion step is exact in both modes.
- *   row_order   row-streaming kernels: 1 each wave takes a contiguous range
+ *   row_order   row-streaming RGB kernels: 1 each wave takes a contiguous range
  *               of output rows; 2 wave q of G takes rows q, q + G, ...
  *               (concurrently running waves stream neighbouring rows);
- *               0 (default): 2 for uniform RGB batches whose staged rows
- *               exceed 2 KiB, else 1
+ *               0 (default): 2 for uniform batches whose staged rows exceed
+ *               2 KiB, else 1. I420 waves always take contiguous ranges
  *   upload      how a ragged batch's descriptor table reaches the device:
  *               0 (default) or 3: no copy, the preprocessing kernel reads the
  *               pinned staging slot itself (one launch per call); 1 a DMA

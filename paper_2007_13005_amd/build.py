@@ -35,8 +35,6 @@ SOURCES = [
     "smol_rows_rgb_u8_range_nhwc.hip",
     "smol_rows_yuv_range.hip",
     "smol_rows_yuv_range_nhwc.hip",
-    "smol_rows_yuv_stride.hip",
-    "smol_rows_yuv_stride_nhwc.hip",
     "smol_host.cpp",
     "smol_pipeline.cpp",
     "smol_jpeg_kernels.hip",

@@ -538,14 +538,16 @@ int run_batch(const std::vector<Desc> &descs, size_t first, size_t count, int no
                     "workgroup", pl.lds_bytes, di.lds_per_block);
     const bool rows = pl.path == smol::PATH_ROWS || pl.path == smol::PATH_YUV_ROWS;
     {
-        // Row order of the row-streaming kernels: interleaved across waves
-        // for uniform batches of long staged rows (memory-bound: the waves
-        // then stream neighbouring rows), contiguous ranges otherwise. (Set
-        // before the occupancy query: the two walks are different kernels.)
+        // Row order of the RGB row-streaming kernels: interleaved across
+        // waves for uniform batches of long staged rows (memory-bound: the
+        // waves then stream neighbouring rows), contiguous ranges otherwise.
+        // 64 frames of 1080p from memory, inputs past the 256 MB cache: 21.8
+        // us interleaved, 24.5 in ranges (20.9 in ranges with half of them
+        // cached). (Set before the occupancy query: the two walks are
+        // different kernels.)
         const int order = g_row_order.load();
-        a.interleave = pl.f16 != SMOL_OUT_U8 &&
-                       (order == 2 || (order == 0 && uniform && pl.path == smol::PATH_ROWS &&
-                                       a.row_groups >= 4));
+        a.interleave = pl.path == smol::PATH_ROWS && pl.f16 != SMOL_OUT_U8 &&
+                       (order == 2 || (order == 0 && uniform && a.row_groups >= 4));
         // Whole-line stores: rows of 16-byte multiples, at least one line
         // long, that are not whole lines themselves, in planes of whole lines.
         const long long rb = 2LL * a.Cw;

@@ -209,7 +209,5 @@ const void *rows_rgb_u8_range(const BatchArgs &a);  // uint8: contiguous ranges 
 const void *rows_rgb_u8_range_nhwc(const BatchArgs &a);
 const void *rows_yuv_range(const BatchArgs &a, int f16);
 const void *rows_yuv_range_nhwc(const BatchArgs &a, int f16);
-const void *rows_yuv_stride(const BatchArgs &a, int f16);
-const void *rows_yuv_stride_nhwc(const BatchArgs &a, int f16);
 
 }  // namespace smol

@@ -867,9 +867,7 @@ int launch_yuv_direct(const BatchArgs &a, int out_type, void *stream, void *done
 
 const void *yuv_rows_kernel_for(const BatchArgs &a, int f16)
 {
-    if (a.nhwc)
-        return a.interleave ? rows_yuv_stride_nhwc(a, f16) : rows_yuv_range_nhwc(a, f16);
-    return a.interleave ? rows_yuv_stride(a, f16) : rows_yuv_range(a, f16);
+    return a.nhwc ? rows_yuv_range_nhwc(a, f16) : rows_yuv_range(a, f16);
 }
 
 // LDS bytes of the column table that the waves of an I420 row-streaming

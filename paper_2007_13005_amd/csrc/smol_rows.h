@@ -42,7 +42,7 @@ namespace {
 // exact integer arithmetic (the numerator grows by a precomputed constant per
 // step): no division per row but the one for the weight.
 //
-// Lane l computes 2J consecutive output columns (lane_col); their taps (byte
+// Lane l computes J pairs of output columns (pair_col); their taps (byte
 // offset in the staged span, weight) stay in registers while the horizontal
 // geometry is unchanged. Each pixel's two horizontal taps are 6 bytes of a
 // staged row, read as three aligned dwords and realigned.
@@ -109,47 +109,57 @@ __device__ __forceinline__ RowImg row_img(const BatchArgs &a, int img, int strip
     return g;
 }
 
-// First of the strip's columns that lane `lane` computes: 2J consecutive
-// columns from 2 J lane on, clamped so that they end at the strip's last
-// column (cols >= 2J, or cols = 1 with J = 1). Lanes past the strip thus
-// compute and store columns that other lanes store as well, the same values
-// to the same addresses: every lane runs the same stores, with no branch
-// around them, and the compiler can count the memory operations in flight
-// exactly (a branch that might skip the stores would make it wait for them
-// before every write to LDS).
-template <int J>
-__device__ __forceinline__ int lane_col(int lane, int cols)
+// Column px of column pair j that lane `lane` computes. QUADS (J = 2): four
+// consecutive columns from 4 lane on, so that a plane's store is 4 columns wide;
+// else pair j is the columns from 2 lane + 128 j on, so that an interleaved
+// (NHWC) row's stores of pair j lie side by side (fp32 pixels of four columns
+// per lane, stored 48 bytes apart, took twice as long: 101 upscales 110 -> 224
+// 48.8 against 21.6 us). Clamped so that the columns end at the strip's last
+// (cols >= 2J, or cols = 1 with J = 1). Lanes past the strip thus compute and
+// store columns that other lanes store as well, the same values to the same
+// addresses: every lane runs the same stores, with no branch around them, and
+// the compiler can count the memory operations in flight exactly (a branch that
+// might skip the stores would make it wait for them before every write to LDS).
+template <int J, bool QUADS>
+__device__ __forceinline__ int pair_col(int lane, int j, int cols)
 {
-    return min(2 * J * lane, max(cols - 2 * J, 0));
+    return QUADS ? min(2 * J * lane, max(cols - 2 * J, 0)) + 2 * j
+                 : min(2 * lane + 128 * j, max(cols - 2, 0));
 }
 
-// Column taps of the lane's 2J consecutive columns: one division for the first
-// (floor quotient and remainder of num = (2 (left + c) + 1) W - Wr by
-// den = 2 Wr), exact integer steps for the others. The weight rem / den
-// rounded to nearest fp32 comes from an fp64 product with RN(1 / den): the
-// product is within 2^-52 (relative) of the quotient, and no such quotient
-// (0 < rem < den <= 2^24) lies within 2^-49 (relative) of a midpoint between
-// fp32 values, so both round to the same fp32 value. (A tap computed on its
-// own costs about 60 instructions, and a wave of a ragged batch walks only a
-// dozen rows with them.)
-template <int J>
+// A column's floor quotient and remainder of num = (2 (left + c) + 1) W - Wr by
+// den = 2 Wr (-den < num < 2^39; the double quotient's truncation is the exact
+// floor: a non-integer quotient is at least 1 / den from the next integer).
+__device__ __forceinline__ void col_divmod(const RowImg &g, int c, int den, int &q, int &rem)
+{
+    const long long num = (long long)(2 * (g.left + c) + 1) * g.W - g.Wr;
+    q = num < 0               ? -1
+        : num < 0x7fffffffLL ? (int)((unsigned)num / (unsigned)den)
+                             : (int)((double)num / (double)den);
+    rem = (int)(num - (long long)q * den);
+}
+
+// Column taps of a lane's columns: one division per run of consecutive columns
+// and exact integer steps within it. The weight rem / den rounded to nearest
+// fp32 comes from an fp64 product with RN(1 / den): the product is within 2^-52
+// (relative) of the quotient, and no such quotient (0 < rem < den <= 2^24) lies
+// within 2^-49 (relative) of a midpoint between fp32 values, so both round to
+// the same fp32 value. (A tap computed on its own costs about 60 instructions,
+// and a wave of a ragged batch walks only a dozen rows with them.)
+template <int J, bool QUADS>
 __device__ __forceinline__ void row_taps(const RowImg &g, const int cols, int (&cx)[J][2],
                                          float (&cw)[J][2], int lane)
 {
     const int den = 2 * g.Wr;
     const double rcp = 1.0 / (double)den;
-    const long long num = (long long)(2 * (g.left + lane_col<J>(lane, cols)) + 1) * g.W - g.Wr;
-    // -den < num < 2^39; the double quotient's truncation is the exact floor
-    // (a non-integer quotient is at least 1 / den from the next integer)
-    int q = num < 0               ? -1
-            : num < 0x7fffffffLL ? (int)((unsigned)num / (unsigned)den)
-                                 : (int)((double)num / (double)den);
-    int rem = (int)(num - (long long)q * den);
     // a crop of one column computes it twice
     const int step = cols > 1 ? 2 * g.W : 0;
     const int qs = step / den, rs = step - qs * den;
+    int q, rem;
 #pragma unroll
-    for (int j = 0; j < J; ++j)
+    for (int j = 0; j < J; ++j) {
+        if (j == 0 || !QUADS)
+            col_divmod(g, pair_col<J, QUADS>(lane, j, cols), den, q, rem);
 #pragma unroll
         for (int px = 0; px < 2; ++px) {
             const bool low = q < 0, high = q >= g.W - 1;
@@ -161,6 +171,7 @@ __device__ __forceinline__ void row_taps(const RowImg &g, const int cols, int (&
             rem -= carry ? den : 0;
             q += carry ? 1 : 0;
         }
+    }
 }
 
 // Pixels x0 (bytes 0..2) and x0 + 1 (bytes 3..5) of an 8-byte window, as
@@ -241,20 +252,13 @@ struct StagedRows {
     float wy;
 };
 
-// The rows a wave walks: batch rows r0, r0 + d, r0 + 2d, ... as (image, crop
-// row) pairs, which advance by (d / Ch, d % Ch) per step. STRIDE = 0: d = 1,
-// a wave takes a contiguous range of rows. STRIDE = 1: d = the number of
-// waves G, wave q takes rows q, q + G, ..., so at any moment the waves work
-// on a band of consecutive output rows, close together in memory.
+// The rows a wave of the strided walk takes: batch rows q, q + G, q + 2G, ...
+// (G waves) as (image, crop row) pairs, which advance by (G / Ch, G % Ch) per
+// step, so at any moment the waves work on a band of consecutive output rows,
+// close together in memory.
 struct RowStep {
     int di, dr, Ch;
 };
-
-template <int STRIDE>
-__device__ __forceinline__ RowStep row_step_of(const BatchArgs &a)
-{
-    return STRIDE ? RowStep{a.step_di, a.step_dr, a.Ch} : RowStep{0, 1, a.Ch};
-}
 
 // First row and row count of wave `w`: the host splits the n * Ch rows as
 // rows_q * grid + rows_r, so every wave walks rows_q rows and waves
@@ -267,18 +271,16 @@ __device__ __forceinline__ void wave_rows(const BatchArgs &a, int w, long long &
     r0 = STRIDE ? (long long)w : (long long)w * a.rows_q + min(w, a.rows_r);
 }
 
-// Image and crop row of batch row r (r < 2^31 in a strided walk, where it is
-// a wave index).
-template <int STRIDE>
+// Image and crop row of batch row r. (A 64-bit division takes about 140 scalar
+// instructions before a wave's first load, so it stands aside for rows past
+// 2^32.)
 __device__ __forceinline__ void split_row(long long r, int Ch, int &img, int &rr)
 {
-    if (STRIDE) {
+    if ((unsigned long long)r >> 32 == 0)
         img = (int)((unsigned)r / (unsigned)Ch);
-        rr = (int)r - img * Ch;
-    } else {
+    else
         img = (int)(r / Ch);
-        rr = (int)(r - (long long)img * Ch);
-    }
+    rr = (int)(r - (long long)img * Ch);
 }
 
 // Workgroups are dealt to the 8 XCDs round-robin; remap so the waves of one
@@ -320,7 +322,7 @@ __device__ __forceinline__ void floor_divmod(long long n, int d, int &q, int &r)
     r = (int)rr;
 }
 
-// Vertical half-pixel taps along a walk over rows of one geometry:
+// Vertical half-pixel taps along a strided walk over rows of one geometry:
 // num(rr) = (2 * (top + rr) + 1) * H - Hr, den = 2 * Hr, q = floor(num / den),
 // rem = num - q * den. A step moves rr by dr, or by dr - Ch when it wraps to
 // the next image of the same geometry, so num by one of two constants whose
@@ -329,28 +331,24 @@ __device__ __forceinline__ void floor_divmod(long long n, int d, int &q, int &r)
 struct VCursor {
     int q, rem, den, H;
     int qs, rs;    // step within an image
-    int qw, rw;    // step that wraps (strided walks of a uniform batch)
+    int qw, rw;    // step that wraps (a uniform batch)
 };
 
-template <int STRIDE>
 __device__ __forceinline__ void vcursor_init(VCursor &v, const BatchArgs &a, const RowImg &g, int rr,
                                              const RowStep &s)
 {
     const int den = 2 * g.Hr;
     int q, rem, qs, rs, qw = 0, rw = 0;
     floor_divmod((long long)(2 * (g.top + rr) + 1) * g.H - g.Hr, den, q, rem);
-    if (STRIDE && !a.table) {
+    if (!a.table) {
         // one geometry for the whole launch: the host computed the steps
         qs = a.vq_s;
         rs = a.vr_s;
         qw = a.vq_w;
         rw = a.vr_w;
-    } else if (STRIDE) {
+    } else {
         // a walk over a table reads the next image's descriptor on a wrap
         floor_divmod(2LL * g.H * s.dr, den, qs, rs);
-    } else {
-        qs = (2 * g.H) / den;
-        rs = 2 * g.H - qs * den;
     }
     // (every field stored on every path: stores that differ by branch can be
     // merged into one store to a chosen field, which keeps the cursor in
@@ -398,7 +396,7 @@ __device__ __forceinline__ void cursor_image(RowCursor &c, const BatchArgs &a, i
     const RowImg g = row_img(a, img, (int)blockIdx.y);
     c.img = img;
     c.rr = rr;
-    vcursor_init<1>(c.v, a, g, rr, s);
+    vcursor_init(c.v, a, g, rr, s);
     c.base = (uintptr_t)(a.src + g.off) + 3 * (uintptr_t)g.xf;
     c.pitch = g.pitch;
     c.span = g.span;
@@ -632,7 +630,7 @@ __device__ __forceinline__ void pack_pair(RowOut<F16, J> &out, int j, const floa
     }
 }
 
-// Store a lane's 2J consecutive columns of one output row: per plane (NCHW) or
+// Store a lane's columns (pair_col) of one output row: per plane (NCHW) or
 // interleaved (NHWC), in the widest stores that hold them (4 columns of fp16:
 // 8 bytes per plane). The addresses are aligned to an element only: crop
 // widths and strips are arbitrary, and global stores take any alignment.
@@ -669,7 +667,7 @@ __device__ __forceinline__ void store_row(uint8_t *orow, long long plane, int co
 {
     static_assert(J == 1 || J == 2, "one or two column pairs per lane");
     constexpr int kEsz = F16 == 2 ? 1 : F16 ? 2 : 4;
-    const int c = lane_col<J>(lane, cols);
+    const int c = pair_col<J, true>(lane, 0, cols);
     if constexpr (ONE) {
 #pragma unroll
         for (int ch = 0; ch < 3; ++ch) {
@@ -722,27 +720,21 @@ __device__ __forceinline__ void store_row(uint8_t *orow, long long plane, int co
             store_words<3, false>(dst, u32x3{lo[0], hi[0] | lo[J - 1] << 16,
                                              lo[J - 1] >> 16 | hi[J - 1] << 16});
         }
-    } else if constexpr (F16) {
-        u32x3 w[J];
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const uint32_t w0 = out.word(0, j), w1 = out.word(1, j), w2 = out.word(2, j);
-            w[j] = u32x3{(w0 & 0xffffu) | (w1 << 16), (w2 & 0xffffu) | (w0 & 0xffff0000u),
-                         (w1 >> 16) | (w2 & 0xffff0000u)};
-        }
-        if constexpr (J == 1) {
-            store_words<3>(dst, w[0]);
-        } else {
-            store_words<4>(dst, u32x4{w[0].x, w[0].y, w[0].z, w[J - 1].x});
-            store_words<2>(dst + 16, u32x2{w[J - 1].y, w[J - 1].z});
-        }
     } else {
-        // two pixels: r g b r g b
 #pragma unroll
         for (int j = 0; j < J; ++j) {
-            store_words<4>(dst + 24 * j, u32x4{out.word(0, j), out.word(1, j), out.word(2, j),
-                                               out.word(0, j, 1)});
-            store_words<2>(dst + 24 * j + 16, u32x2{out.word(1, j, 1), out.word(2, j, 1)});
+            // two pixels: r g b r g b
+            uint8_t *dj = orow + 3u * (uint32_t)pair_col<J, false>(lane, j, cols) * kEsz;
+            if constexpr (F16) {
+                const uint32_t w0 = out.word(0, j), w1 = out.word(1, j), w2 = out.word(2, j);
+                store_words<3>(dj, u32x3{(w0 & 0xffffu) | (w1 << 16),
+                                         (w2 & 0xffffu) | (w0 & 0xffff0000u),
+                                         (w1 >> 16) | (w2 & 0xffff0000u)});
+            } else {
+                store_words<2>(dj, u32x2{out.word(0, j), out.word(1, j)});
+                store_words<2>(dj + 8, u32x2{out.word(2, j), out.word(0, j, 1)});
+                store_words<2>(dj + 16, u32x2{out.word(1, j, 1), out.word(2, j, 1)});
+            }
         }
     }
 }
@@ -832,11 +824,11 @@ struct RowRecs {
     uint32_t kind;    // span << 2 | relation to the previous row
 };
 
-// Records of the 64 rows from crop row rr of image img on (rows past the
-// batch's end are left unset). An image's first row and the first record are
-// kRowNew.
+// Records of the next `count` rows, at most 64, from crop row rr of image img
+// on. An image's first row and the first record are kRowNew. (Only the images
+// of those rows are visited: a ragged batch's descriptors come over the bus.)
 __device__ __forceinline__ void row_records(RowRecs &t, const BatchArgs &a, int img, int rr,
-                                            int lane, int strip)
+                                            int count, int lane, int strip)
 {
     const int Ch = a.Ch;
     int first = 0;  // the record of crop row rr of image img
@@ -860,8 +852,9 @@ __device__ __forceinline__ void row_records(RowRecs &t, const BatchArgs &a, int 
         }
         first += Ch - rr;
         rr = 0;
-        if (first >= 64 || ++img >= a.n)
+        if (first >= min(count, 64))
             break;
+        ++img;
     }
     const int p0 = __shfl_up(y0, 1, 64), p1 = __shfl_up(y1, 1, 64);
     t.kind |= fresh                    ? kRowNew

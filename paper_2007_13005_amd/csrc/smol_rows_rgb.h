@@ -14,6 +14,7 @@ template <int F16, int J, int EXACT, int G, int P, int FORM>
 __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_stride_kernel(BatchArgs a)
 {
     constexpr int NHWC = FORM & kFormNhwc, ONE = (FORM & kFormOne) ? 1 : 0;
+    constexpr bool QUADS = !NHWC || F16 == 2;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_all[];
     int lane;
     long long r0;
@@ -24,10 +25,10 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_stride_kernel(
     // early exit here would hold the remaining argument loads behind it).
     __builtin_assume(n_rows > 0);
     const int strip = (int)blockIdx.y;
-    const RowStep step = row_step_of<1>(a);
+    const RowStep step{a.step_di, a.step_dr, Ch};
     constexpr int kEsz = F16 == 2 ? 1 : F16 ? 2 : 4;
     int c_img, c_rr;  // row to interpolate
-    split_row<1>(r0, Ch, c_img, c_rr);
+    split_row(r0, Ch, c_img, c_rr);
     RowCursor lc;  // next row to load
     cursor_image(lc, a, c_img, c_rr, step);
 
@@ -69,7 +70,7 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_stride_kernel(
     int cW, cWr, cleft;
     {
         const RowImg g = row_img(a, c_img, strip);
-        row_taps<J>(g, a.strip_w, cx, cw, lane);
+        row_taps<J, QUADS>(g, a.strip_w, cx, cw, lane);
         cW = g.W;
         cWr = g.Wr;
         cleft = g.left;
@@ -118,7 +119,7 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_stride_kernel(
                 cW = g.W;                                                                     \
                 cWr = g.Wr;                                                                   \
                 cleft = g.left;                                                               \
-                row_taps<J>(g, a.strip_w, cx, cw, lane);                                      \
+                row_taps<J, QUADS>(g, a.strip_w, cx, cw, lane);                               \
             }                                                                                 \
         }                                                                                     \
     }
@@ -166,6 +167,7 @@ template <int F16, int J, int EXACT, int G, int FORM>
 __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_range_kernel(BatchArgs a)
 {
     constexpr int NHWC = FORM & kFormNhwc, ONE = (FORM & kFormOne) ? 1 : 0;
+    constexpr bool QUADS = !NHWC || F16 == 2;
     constexpr bool LINES = (FORM & kFormLines) != 0;
     static_assert(!LINES || (F16 == 1 && !NHWC && !ONE), "whole lines: fp16 NCHW");
     constexpr int kEsz = F16 == 2 ? 1 : F16 ? 2 : 4;
@@ -181,10 +183,10 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_range_kernel(B
     __builtin_assume(n_rows > 0);
     const int strip = (int)blockIdx.y;
     int c_img, c_rr;  // row to interpolate
-    split_row<0>(r0, Ch, c_img, c_rr);
+    split_row(r0, Ch, c_img, c_rr);
 
     RowRecs recs;
-    row_records(recs, a, c_img, c_rr, lane, strip);
+    row_records(recs, a, c_img, c_rr, n_rows, lane, strip);
     // A row's scalars: offset of each source row's first byte in its first
     // chunk, vertical weight, relation to the previous row.
     struct RowS {
@@ -206,8 +208,8 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_range_kernel(B
         const bool past = li >= n_rows;
         if (!past && li != 0 && (li & 63) == 0) {
             int img, rr;
-            split_row<0>(r0 + li, Ch, img, rr);
-            row_records(recs, a, img, rr, lane, strip);
+            split_row(r0 + li, Ch, img, rr);
+            row_records(recs, a, img, rr, n_rows - li, lane, strip);
         }
         const int i = min(li, n_rows - 1) & 63;
         const uint32_t lo = __builtin_amdgcn_readlane(recs.lo, i);
@@ -262,7 +264,7 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_range_kernel(B
     int cW, cWr, cleft;
     {
         const RowImg g = row_img(a, c_img, strip);
-        row_taps<J>(g, a.strip_w, cx, cw, lane);
+        row_taps<J, QUADS>(g, a.strip_w, cx, cw, lane);
         cW = g.W;
         cWr = g.Wr;
         cleft = g.left;
@@ -303,7 +305,7 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_range_kernel(B
     uint8_t *const ring = lds + 2048 * G;
     uint32_t pos = LINES ? (uint32_t)(uintptr_t)orow & 127u : 0u;  // the row's first byte
     uint32_t done = pos;                                          // bytes stored so far
-    const uint32_t lane_out = LINES ? 2u * (uint32_t)lane_col<J>(lane, a.strip_w) : 0u;
+    const uint32_t lane_out = LINES ? 2u * (uint32_t)pair_col<J, true>(lane, 0, a.strip_w) : 0u;
     // store the row; `last`: the wave's last row
     auto store = [&](bool last) {
         if constexpr (!LINES) {
@@ -354,7 +356,7 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_range_kernel(B
                 cW = g.W;
                 cWr = g.Wr;
                 cleft = g.left;
-                row_taps<J>(g, a.strip_w, cx, cw, lane);
+                row_taps<J, QUADS>(g, a.strip_w, cx, cw, lane);
             }
         }
     }

@@ -9,7 +9,7 @@ namespace smol {
 namespace {
 
 // ---------------------------------------------------------------------------
-// I420, row streaming: one wave per workgroup, the scheme of the RGB kernel.
+// I420, row streaming: the scheme of the RGB kernel's contiguous walk.
 //
 // For each output row the wave loads eight row segments into registers and
 // then into its LDS slot (1 KiB each): luma rows y0 and y1 over the crop's
@@ -32,12 +32,19 @@ namespace {
 // weight bytes; the BT.601 products then use the coefficients divided by 16,
 // which gives the same real products and so the same rounded values.
 //
-// Lane l computes output columns c = 2l + 128j and c + 1 (j < J). Per column
-// it keeps: the luma tap (offset of x0 in the staged luma span, weight), and
+// Lane l computes J pairs of output columns (pair_col). Per column it keeps: the luma tap (offset of x0 in the staged luma span, weight), and
 // for its two luma columns x0, x1 the offset of the first chroma column they
 // read, per luma column a v_perm selector that picks its two chroma samples
 // from each of two chroma rows, and its horizontal weight bytes
 // (4 - fx, fx).
+//
+// Bound by VALU issue: without its loads and stores it takes as long (128
+// frames of 720p: 32.1 us, 32.4 without either, 10.8 without the arithmetic).
+// 462 of a row's 495 vector instructions are the definition's arithmetic and
+// the reads; with the rows' taps computed 64 at a time the walk takes 35 and 116
+// scalar ones (64 and 199 with a cursor): 32.0 -> 31.5 us, 4K strips 17.4 -> 17.1.
+// Loading after the stores' row is staged (as for RGB), 2 or 4 waves per SIMD and
+// the ILP scheduler are no faster.
 // ---------------------------------------------------------------------------
 // A frame's plane offsets and the processed region: W x H luma pixels at
 // (rx, ry) in a frame of fw x fh (chroma taps use frame coordinates).
@@ -108,34 +115,19 @@ struct YuvStaged {
     int fy0, fy1;  // weights of chroma rows r1 (in y0's pair) and r2 (in y1's), in quarters
 };
 
-// Load cursor over the output rows of I420 frames (the walk of the RGB
-// cursor, with the three plane bases).
-struct YuvCursor {
-    int img, rr;
-    VCursor v;          // luma vertical map over the region's rows
-    double rcp;         // 1 / v.den, rounded to nearest
-    uintptr_t base[3];  // first staged byte of the region's row 0 (Y), of chroma row 0 (Cb, Cr)
-    int W, Wc, Hc, yspan, cspan;  // frame luma pitch, chroma pitch and rows
-    int ry;             // the region's first frame row
+// The image a wave loads rows of: the three planes' first staged bytes (the
+// region's row 0 of Y, chroma row 0 of Cb and Cr), the luma and chroma pitches
+// and the spans.
+struct YuvLoad {
+    uintptr_t base[3];
+    int W, Wc, yspan, cspan;
 };
 
-template <int STRIDE>
-__device__ __forceinline__ void yuv_cursor_image(YuvCursor &c, const BatchArgs &a, int img, int rr,
-                                                 const RowStep &s)
+__device__ __forceinline__ void yuv_load_image(YuvLoad &c, const BatchArgs &a, int img, int strip)
 {
-    const YuvImg g = yuv_img(a, img, (int)blockIdx.y);
-    c.img = img;
-    c.rr = rr;
-    RowImg lg{};
-    lg.H = g.H;
-    lg.Hr = g.Hr;
-    lg.top = g.top;
-    vcursor_init<STRIDE>(c.v, a, lg, rr, s);
-    c.rcp = 1.0 / (double)c.v.den;
+    const YuvImg g = yuv_img(a, img, strip);
     c.W = g.fw;
     c.Wc = (g.fw + 1) >> 1;
-    c.Hc = (g.fh + 1) >> 1;
-    c.ry = g.ry;
     const int cxf = chroma_tap(g.rx + g.xf, c.Wc, a.siting).x0;
     const int cxl = chroma_tap(g.rx + g.xf + g.span - 1, c.Wc, a.siting).x1;
     c.yspan = g.span;
@@ -146,35 +138,17 @@ __device__ __forceinline__ void yuv_cursor_image(YuvCursor &c, const BatchArgs &
     c.base[2] = (uintptr_t)(a.src + g.off[2]) + (uintptr_t)cxf;
 }
 
-template <int STRIDE>
-__device__ __forceinline__ void yuv_cursor_next(YuvCursor &c, const BatchArgs &a, const RowStep &s)
-{
-    if (!STRIDE) {
-        vcursor_add(c.v, c.v.qs, c.v.rs);
-        if (++c.rr == s.Ch && c.img + 1 < a.n)
-            yuv_cursor_image<0>(c, a, c.img + 1, 0, s);
-        return;
-    }
-    const int img0 = c.img;
-    c.img += s.di;
-    c.rr += s.dr;
-    const bool wrapped = c.rr >= s.Ch;
-    if (wrapped) {
-        c.rr -= s.Ch;
-        ++c.img;
-    }
-    if (!a.table) {
-        const uintptr_t d = (uintptr_t)(c.img - img0) * (uintptr_t)a.stride;
-        c.base[0] += d;
-        c.base[1] += d;
-        c.base[2] += d;
-        vcursor_add(c.v, wrapped ? c.v.qw : c.v.qs, wrapped ? c.v.rw : c.v.rs);
-    } else if (c.img != img0) {
-        yuv_cursor_image<1>(c, a, c.img, c.rr, s);
-    } else {
-        vcursor_add(c.v, c.v.qs, c.v.rs);
-    }
-}
+// The rows of the walk, one per lane, up to 64 at once (as row_records for
+// RGB): a row's taps cost one pass of the whole wave per 64 rows instead of a
+// cursor's steps and three clamped taps per row.
+struct YuvRecs {
+    uint32_t yoff;  // luma row y0's byte offset from the region's row 0
+    uint32_t coff;  // chroma row r0's byte offset
+    float wy;
+    // bit 0: y1 = y0 + 1; bit 1: r1 = r0 + 1; bits 2, 3: r2 - r1 + 1; bits 4, 5
+    // and 6 to 8: weights of r1 (in y0's pair) and r2 (in y1's), in quarters
+    uint32_t bits;
+};
 
 // LDS layout of a wave's slot: luma segments of 1 KiB * GL, then the six
 // chroma segments of 1 KiB.
@@ -203,41 +177,60 @@ __device__ __forceinline__ void chroma_rows(int y, int n, int &r0, int &r1, int 
     }
 }
 
-template <int GL>
-__device__ __forceinline__ void yuv_load(YuvStaged<GL> &st, const YuvCursor &c, int lane,
-                                         bool repeat)
+// Records of the next `count` rows, at most 64, from crop row rr of image img
+// on.
+__device__ __forceinline__ void yuv_records(YuvRecs &t, const BatchArgs &a, int img, int rr,
+                                            int count, int lane, int strip)
 {
-    int y0, y1;
-    if (c.v.q < 0 || (c.v.q == 0 && c.v.rem == 0)) {
-        y0 = y1 = 0;
-        st.wy = 0.0f;
-    } else if (c.v.q >= c.v.H - 1) {
-        y0 = y1 = c.v.H - 1;
-        st.wy = 0.0f;
-    } else {
-        y0 = c.v.q;
-        y1 = y0 + 1;
-        // rem / den rounded to nearest fp32 (0 < rem < den <= 2^24): the
-        // fp64 product rem * RN(1 / den) is within 2^-52 (relative) of the
-        // quotient, and no such quotient lies within 2^-49 (relative) of a
-        // midpoint between fp32 values (that would need 2^25 | den), so
-        // both round to the same fp32 value
-        st.wy = (float)((double)c.v.rem * c.rcp);
+    const int Ch = a.Ch;
+    int first = 0;  // the record of crop row rr of image img
+    while (true) {
+        const YuvImg g = yuv_img(a, img, strip);
+        const int r = rr + lane - first;
+        const Tap ty = axis_tap(g.top + r, g.H, g.Hr);
+        if (lane >= first && r < Ch) {
+            const int Wc = (g.fw + 1) >> 1, Hc = (g.fh + 1) >> 1;
+            int a0, a1, f0, b0, b1, f1;
+            chroma_rows(g.ry + ty.x0, Hc, a0, a1, f0);
+            chroma_rows(g.ry + ty.x1, Hc, b0, b1, f1);
+            // y1's taps move on by one chroma row (b0 == a1) or keep y0's
+            // second row (b1 == a1); y1 reads (r1 = a1, r2) either way
+            const bool next = b0 == a1;
+            const int r2 = next ? b1 : b0, w2 = next ? f1 : 4 - f1;
+            t.yoff = (uint32_t)ty.x0 * (uint32_t)g.fw;
+            t.coff = (uint32_t)a0 * (uint32_t)Wc;
+            t.wy = ty.w;
+            t.bits = (uint32_t)(ty.x1 - ty.x0) | (uint32_t)(a1 - a0) << 1 |
+                     (uint32_t)(r2 - a1 + 1) << 2 | (uint32_t)f0 << 4 | (uint32_t)w2 << 6;
+        }
+        first += Ch - rr;
+        rr = 0;
+        if (first >= min(count, 64))
+            break;
+        ++img;
     }
-    int a0, a1, f0, b0, b1, f1;
-    chroma_rows(c.ry + y0, c.Hc, a0, a1, f0);
-    chroma_rows(c.ry + y1, c.Hc, b0, b1, f1);
-    // y1's taps move on by one chroma row (b0 == a1) or keep y0's second row
-    // (b1 == a1); y1 reads (r1 = a1, r2) either way
-    const bool next = b0 == a1;
-    const int r2 = next ? b1 : b0;
-    st.fy0 = f0;
-    st.fy1 = next ? f1 : 4 - f1;
-    const uintptr_t row[8] = {
-        c.base[0] + (uintptr_t)y0 * (uintptr_t)c.W,  c.base[0] + (uintptr_t)y1 * (uintptr_t)c.W,
-        c.base[1] + (uintptr_t)a0 * (uintptr_t)c.Wc, c.base[1] + (uintptr_t)a1 * (uintptr_t)c.Wc,
-        c.base[1] + (uintptr_t)r2 * (uintptr_t)c.Wc, c.base[2] + (uintptr_t)a0 * (uintptr_t)c.Wc,
-        c.base[2] + (uintptr_t)a1 * (uintptr_t)c.Wc, c.base[2] + (uintptr_t)r2 * (uintptr_t)c.Wc};
+}
+
+// Loads the row of record i. `past`: the row was loaded already (past the end
+// of the wave's range); the lanes then load the segments' first chunks, so the
+// instruction stream is unchanged but almost nothing is fetched.
+template <int GL>
+__device__ __forceinline__ void yuv_load(YuvStaged<GL> &st, const YuvLoad &c, const YuvRecs &t,
+                                         int i, int lane, bool past)
+{
+    const uint32_t yoff = __builtin_amdgcn_readlane(t.yoff, i);
+    const uint32_t coff = __builtin_amdgcn_readlane(t.coff, i);
+    const uint32_t bits = __builtin_amdgcn_readlane(t.bits, i);
+    st.wy = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(t.wy), i));
+    st.fy0 = (int)(bits >> 4 & 3u);
+    st.fy1 = (int)(bits >> 6);
+    const uint32_t d1 = bits & 1u ? (uint32_t)c.W : 0u;
+    const uint32_t c1 = coff + (bits & 2u ? (uint32_t)c.Wc : 0u);
+    const uint32_t s2 = bits >> 2 & 3u;
+    const uint32_t c2 = s2 == 0u ? c1 - (uint32_t)c.Wc : s2 == 1u ? c1 : c1 + (uint32_t)c.Wc;
+    const uintptr_t row[8] = {c.base[0] + yoff, c.base[0] + yoff + d1, c.base[1] + coff,
+                              c.base[1] + c1,   c.base[1] + c2,        c.base[2] + coff,
+                              c.base[2] + c1,   c.base[2] + c2};
     typedef __attribute__((address_space(1))) const uint8_t GlobalByte;
     typedef const __attribute__((address_space(1))) u32x4 GlobalChunk;
     const uint32_t lane16 = 16u * (uint32_t)lane;
@@ -247,8 +240,8 @@ __device__ __forceinline__ void yuv_load(YuvStaged<GL> &st, const YuvCursor &c, 
         // byte offset of the lane's chunk: lanes past the segment's last
         // chunk load that chunk again
         const uint32_t last16 =
-            repeat ? 0u : (uint32_t)(st.sh[s] + (s < 2 ? c.yspan : c.cspan) - 1) & ~15u;
-        GlobalByte *p = (GlobalByte *)(row[s] - (uintptr_t)st.sh[s]);
+            past ? 0u : (uint32_t)(st.sh[s] + (s < 2 ? c.yspan : c.cspan) - 1) & ~15u;
+        GlobalByte *p = (GlobalByte *)(row[s] & ~(uintptr_t)15);
         // chroma rows are shared by consecutive output rows (a chroma row
         // covers two luma rows): ordinary loads, so the next row's loads of
         // the same rows hit in the caches; luma rows are streamed once
@@ -284,13 +277,13 @@ struct YuvCols {
 
 // The column data of pixel px of column iteration j (one column of the lane)
 // as 8 words: ox, wx (bits), oc, sel[0], sel[1], hw[0], hw[1], 0.
-template <int J>
+template <int J, bool QUADS>
 __device__ __forceinline__ void yuv_col(uint32_t (&w)[8], const YuvImg &g, int cols, int lane,
                                         int siting, int j, int px)
 {
     const int Wc = (g.fw + 1) >> 1;
     const int cxf = chroma_tap(g.rx + g.xf, Wc, siting).x0;
-    const int c = min(lane_col<J>(lane, cols) + 2 * j + px, cols - 1);
+    const int c = min(pair_col<J, QUADS>(lane, j, cols) + px, cols - 1);
     const Tap t = axis_tap(g.left + c, g.W, g.Wr);
     const Tap a0 = chroma_tap(g.rx + t.x0, Wc, siting), a1 = chroma_tap(g.rx + t.x1, Wc, siting);
     w[0] = (uint32_t)(t.x0 - g.xf);
@@ -322,7 +315,7 @@ __device__ __forceinline__ void yuv_col_set(YuvCols<J> &k, int j, int px, const 
     k.hw[j][px][1] = w[6];
 }
 
-template <int J>
+template <int J, bool QUADS>
 __device__ __forceinline__ void yuv_cols(YuvCols<J> &k, const YuvImg &g, int cols, int lane,
                                          int siting)
 {
@@ -331,7 +324,7 @@ __device__ __forceinline__ void yuv_cols(YuvCols<J> &k, const YuvImg &g, int col
 #pragma unroll
         for (int px = 0; px < 2; ++px) {
             uint32_t w[8];
-            yuv_col<J>(w, g, cols, lane, siting, j, px);
+            yuv_col<J, QUADS>(w, g, cols, lane, siting, j, px);
             yuv_col_set<J>(k, j, px, w);
         }
 }
@@ -349,7 +342,7 @@ __device__ __host__ constexpr uint32_t yuv_col_table_bytes()
 // then every wave reads all of them (each pixel's data is the same for every
 // wave's lane). The barrier waits for this wave's LDS writes only, not for
 // the row loads already in flight.
-template <int J>
+template <int J, bool QUADS>
 __device__ __forceinline__ void yuv_cols_shared(YuvCols<J> &k, uint8_t *table, const YuvImg &g,
                                                 int cols, int lane, int siting, int wid, int wpg)
 {
@@ -357,7 +350,7 @@ __device__ __forceinline__ void yuv_cols_shared(YuvCols<J> &k, uint8_t *table, c
     for (int t = 0; t < 2 * J; ++t)
         if (t % wpg == wid) {
             uint32_t w[8];
-            yuv_col<J>(w, g, cols, lane, siting, t / 2, t & 1);
+            yuv_col<J, QUADS>(w, g, cols, lane, siting, t / 2, t & 1);
             u32x4 *e = (u32x4 *)(table + 32u * (64u * (uint32_t)t + (uint32_t)lane));
             e[0] = u32x4{w[0], w[1], w[2], w[3]};
             e[1] = u32x4{w[4], w[5], w[6], w[7]};
@@ -552,62 +545,68 @@ __device__ __forceinline__ void yuv_compute_row(const NormK &nk, uint32_t slot, 
         yuv_compute<F16, J, EXACT, GL, 0>(nk, slot, sh, wy, fy0, fy1, k, out);
 }
 
-// FORM as for rgb_rows_kernel; GL: chunks per lane of a luma segment (staged
-// luma rows of up to 1 or 2 KiB).
-template <int F16, int J, int EXACT, int STRIDE, int FORM, int GL>
+// Wave w walks a range of consecutive output rows. FORM: kFormNhwc, kFormOne;
+// GL: chunks per lane of a luma segment (staged luma rows of up to 1 or 2 KiB).
+template <int F16, int J, int EXACT, int FORM, int GL>
 __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) __attribute__((amdgpu_waves_per_eu(3)))
 yuv_rows_kernel(BatchArgs a)
 {
     constexpr int NHWC = FORM & kFormNhwc, ONE = (FORM & kFormOne) ? 1 : 0;
+    constexpr bool QUADS = !NHWC;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_all[];
     int lane;
     long long r0;
     int n_rows;
     const int Ch = a.Ch;
-    uint8_t *const lds = rows_wave<STRIDE>(lds_all, yuv_seg<GL>(8), a, lane, r0, n_rows);
+    uint8_t *const lds = rows_wave<0>(lds_all, yuv_seg<GL>(8), a, lane, r0, n_rows);
     // The host launches at most one wave per row, so every wave has rows (an
     // early exit here would hold the remaining argument loads behind it).
     __builtin_assume(n_rows > 0);
     const int strip = (int)blockIdx.y;
-    const RowStep step = row_step_of<STRIDE>(a);
-    constexpr int kEsz = F16 == 2 ? 1 : F16 ? 2 : 4;
+    constexpr int kEsz = F16 ? 2 : 4;
     int c_img, c_rr;  // row to interpolate
-    split_row<STRIDE>(r0, Ch, c_img, c_rr);
-    YuvCursor lc;  // next row to load
-    yuv_cursor_image<STRIDE>(lc, a, c_img, c_rr, step);
+    split_row(r0, Ch, c_img, c_rr);
 
-    // One register set: row k + 1 is loaded before row k is interpolated.
-    // The loop runs the n_rows - 1 steps that stage a next row and leaves
-    // only at its end; the last row is interpolated after it. The first row
-    // is requested before the column taps and the rest of the set-up are
-    // computed.
-    int lrow = 0;
-    auto advance = [&]() {
-        if (lrow + 1 < n_rows) {
-            yuv_cursor_next<STRIDE>(lc, a, step);
-            ++lrow;
-        }
-    };
+    YuvRecs recs;
+    yuv_records(recs, a, c_img, c_rr, n_rows, lane, strip);
+    YuvLoad li;
+    yuv_load_image(li, a, c_img, strip);
+    int next = 0, l_img = c_img, l_rr = c_rr;  // row to load
     YuvStaged<GL> R;
-    yuv_load<GL>(R, lc, lane, false);
-    advance();
+    // Loads the next row; past the wave's last row, that row's first chunks.
+    auto load_next = [&]() {
+        const bool past = next >= n_rows;
+        if (!past && next != 0) {
+            if (++l_rr == Ch) {
+                l_rr = 0;
+                yuv_load_image(li, a, ++l_img, strip);
+            }
+            if ((next & 63) == 0)
+                yuv_records(recs, a, l_img, l_rr, n_rows - next, lane, strip);
+        }
+        yuv_load<GL>(R, li, recs, min(next, n_rows - 1) & 63, lane, past);
+        ++next;
+    };
+    // The first row is requested before the column taps and the rest of the
+    // set-up are computed.
+    load_next();
     // bytes between an image's output rows: Cw elements per plane (NCHW) or
     // 3 Cw (NHWC); a wrap to the next image skips the rest of the image.
     const long long rb = (long long)a.Cw * kEsz, rowb = NHWC ? 3 * rb : rb;
-    const long long imgb = 3LL * Ch * rb;
+    const long long plane = Ch * rb, imgb = 3 * plane;
     uint8_t *orow = (uint8_t *)a.out + (long long)(a.img_base + c_img) * imgb + c_rr * rowb +
                     (long long)strip_start(a, strip) * (NHWC ? 3 : 1) * kEsz;
-    const long long ostep = step.di * imgb + step.dr * rowb, owrap = imgb - Ch * rowb;
+    const long long owrap = NHWC ? 0 : 2 * plane;
 
     YuvCols<J> cols;
     int cW, cWr, cleft;
     {
         const YuvImg g = yuv_img(a, c_img, strip);
         if (!a.table && a.wpg > 1)
-            yuv_cols_shared<J>(cols, lds_all + a.wpg * yuv_seg<GL>(8), g, a.strip_w, lane, a.siting,
+            yuv_cols_shared<J, QUADS>(cols, lds_all + a.wpg * yuv_seg<GL>(8), g, a.strip_w, lane, a.siting,
                                __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), a.wpg);
         else
-            yuv_cols<J>(cols, g, a.strip_w, lane, a.siting);
+            yuv_cols<J, QUADS>(cols, g, a.strip_w, lane, a.siting);
         cW = g.W;
         cWr = g.Wr;
         cleft = g.left;
@@ -615,43 +614,38 @@ yuv_rows_kernel(BatchArgs a)
     const NormK nk = norm_consts(a);
     const uint32_t lds0 = lds_addr(lds);
 
-    const long long plane = (long long)Ch * a.Cw * kEsz;
     RowOut<F16, J> out;
-    yuv_write<GL>(lds, R, lane);
-    int csh[8];
-#pragma unroll
-    for (int s = 0; s < 8; ++s)
-        csh[s] = R.sh[s];
-    float cwy = R.wy;
-    int cfy0 = R.fy0, cfy1 = R.fy1;
-    for (int left = n_rows - 1; left > 0; --left) {
-        yuv_load<GL>(R, lc, lane, false);
-        advance();
-        yuv_compute_row<F16, J, EXACT, GL>(nk, lds0, csh, cwy, cfy0, cfy1, cols, out);
+    int csh[8], cfy0, cfy1;
+    float cwy;
+    // writes the loaded row to LDS and takes over its scalars
+    auto stage = [&]() {
         yuv_write<GL>(lds, R, lane);
-        store_row<F16, J, ONE>(orow, plane, a.strip_w, lane, out, NHWC);
 #pragma unroll
         for (int s = 0; s < 8; ++s)
             csh[s] = R.sh[s];
         cwy = R.wy;
         cfy0 = R.fy0;
         cfy1 = R.fy1;
-        const int pimg = c_img;
-        c_img += step.di;
-        c_rr += step.dr;
-        orow += ostep;
-        if (c_rr >= Ch) {
-            c_rr -= Ch;
+    };
+    stage();
+    // One register set: row k + 1 is loaded before row k is interpolated and
+    // written to LDS after it.
+    for (int left = n_rows - 1; left > 0; --left) {
+        load_next();
+        yuv_compute_row<F16, J, EXACT, GL>(nk, lds0, csh, cwy, cfy0, cfy1, cols, out);
+        stage();
+        store_row<F16, J, ONE>(orow, plane, a.strip_w, lane, out, NHWC);
+        orow += rowb;
+        if (++c_rr == Ch) {
+            c_rr = 0;
             ++c_img;
             orow += owrap;
-        }
-        if (c_img != pimg) {
             const YuvImg g = yuv_img(a, c_img, strip);
             if (g.W != cW || g.Wr != cWr || g.left != cleft) {
                 cW = g.W;
                 cWr = g.Wr;
                 cleft = g.left;
-                yuv_cols<J>(cols, g, a.strip_w, lane, a.siting);
+                yuv_cols<J, QUADS>(cols, g, a.strip_w, lane, a.siting);
             }
         }
     }
@@ -659,28 +653,27 @@ yuv_rows_kernel(BatchArgs a)
     store_row<F16, J, ONE>(orow, plane, a.strip_w, lane, out, NHWC);
 }
 
-
 // a.row_groups: KiB per staged luma row, 1 or 2
-template <int F16, int EXACT, int STRIDE, int NHWC, int GL>
+template <int F16, int EXACT, int NHWC, int GL>
 const void *yuv_rows_g(const BatchArgs &a)
 {
-    return a.col_iters > 1 ? (const void *)yuv_rows_kernel<F16, 2, EXACT, STRIDE, NHWC, GL>
-           : a.Cw > 1      ? (const void *)yuv_rows_kernel<F16, 1, EXACT, STRIDE, NHWC, GL>
-                      : (const void *)yuv_rows_kernel<F16, 1, EXACT, STRIDE, NHWC | kFormOne, GL>;
+    return a.col_iters > 1 ? (const void *)yuv_rows_kernel<F16, 2, EXACT, NHWC, GL>
+           : a.Cw > 1      ? (const void *)yuv_rows_kernel<F16, 1, EXACT, NHWC, GL>
+                      : (const void *)yuv_rows_kernel<F16, 1, EXACT, NHWC | kFormOne, GL>;
 }
 
-template <int F16, int EXACT, int STRIDE, int NHWC>
+template <int F16, int EXACT, int NHWC>
 const void *yuv_rows_f(const BatchArgs &a)
 {
-    return a.row_groups >= 2 ? yuv_rows_g<F16, EXACT, STRIDE, NHWC, 2>(a)
-                             : yuv_rows_g<F16, EXACT, STRIDE, NHWC, 1>(a);
+    return a.row_groups >= 2 ? yuv_rows_g<F16, EXACT, NHWC, 2>(a)
+                             : yuv_rows_g<F16, EXACT, NHWC, 1>(a);
 }
 
-template <int STRIDE, int NHWC>
+template <int NHWC>
 const void *yuv_rows_table(const BatchArgs &a, int f16)
 {
-    return f16 ? (a.exact ? yuv_rows_f<1, 1, STRIDE, NHWC>(a) : yuv_rows_f<1, 0, STRIDE, NHWC>(a))
-               : (a.exact ? yuv_rows_f<0, 1, STRIDE, NHWC>(a) : yuv_rows_f<0, 0, STRIDE, NHWC>(a));
+    return f16 ? (a.exact ? yuv_rows_f<1, 1, NHWC>(a) : yuv_rows_f<1, 0, NHWC>(a))
+               : (a.exact ? yuv_rows_f<0, 1, NHWC>(a) : yuv_rows_f<0, 0, NHWC>(a));
 }
 
 }  // namespace

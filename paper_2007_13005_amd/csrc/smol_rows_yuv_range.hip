@@ -3,6 +3,6 @@
 
 namespace smol {
 
-const void *rows_yuv_range(const BatchArgs &a, int f16) { return yuv_rows_table<0, 0>(a, f16); }
+const void *rows_yuv_range(const BatchArgs &a, int f16) { return yuv_rows_table<0>(a, f16); }
 
 }  // namespace smol

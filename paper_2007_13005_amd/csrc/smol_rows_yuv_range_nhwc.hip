@@ -3,6 +3,6 @@
 
 namespace smol {
 
-const void *rows_yuv_range_nhwc(const BatchArgs &a, int f16) { return yuv_rows_table<0, 1>(a, f16); }
+const void *rows_yuv_range_nhwc(const BatchArgs &a, int f16) { return yuv_rows_table<1>(a, f16); }
 
 }  // namespace smol
