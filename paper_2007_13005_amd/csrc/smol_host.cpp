@@ -586,8 +586,14 @@ int run_batch(const std::vector<Desc> &descs, size_t first, size_t count, int no
                 // Small launches: at least about three rows per wave, in
                 // multiples of 4 waves per compute unit (a wave's set-up and
                 // first load cost about a row; 7,168 rows of 224 columns take
-                // 8.1 us on 5,120 waves and 6.7 us on 2,048).
-                const long long by_rows = items * S / kRowsMinPerWave / di.cus;
+                // 8.1 us on 5,120 waves and 6.7 us on 2,048). Where that
+                // leaves fewer than 8 waves per compute unit the chip idles
+                // on the longest chain instead, so one row is enough: 4,480
+                // rows take 7.8 us on 1,024 waves and 6.7 us on 4,096 (I420:
+                // 11.9 and 8.8 us), 6,048 rows 8.9 and 7.6 us.
+                long long by_rows = items * S / kRowsMinPerWave / di.cus;
+                if (by_rows < 8)
+                    by_rows = items * S / di.cus;
                 if (by_rows < waves)
                     waves = (int)std::min<long long>(waves,
                                                      std::max<long long>(4, by_rows & ~3LL));
