@@ -384,18 +384,33 @@ struct Plan {
     int f16;
 };
 
-// The column strips of a row-streaming launch, at least `least` of them. A
-// crop of more than kStripCols columns splits into strips of 256 columns (two
-// column pairs per lane) or, where that leaves an odd number of 128-column
-// halves, of 128 (one pair per lane), which fill every lane and start at whole
-// 128-byte lines of fp16 output; the last strip ends at the last column and
-// overlaps its neighbour. More strips than that (long source spans) have equal
-// widths. 32 frames of 720p to 640 x 640: 37.0 us in 5 strips of 128, 40.7 in
-// 3 of 216, 43.6 in 4 of 160 (61 us on the register-gather kernel).
-void plan_strips(int Cw, int least, int *strips, int *strip_w)
+// The column strips of a row-streaming launch, at least `least` of them.
+// Strips of one width: a start at a multiple of it, the last strip ends at the
+// last column and overlaps its neighbour.
+//   I420: 256 columns (two column pairs per lane) or, where that leaves an odd
+//     number of 128-column halves, 128 (one pair per lane).
+//   RGB, 385-512 columns: 256. Elsewhere the fewest strips of up to 256
+//     columns in equal widths, of whole 128-byte float lines where the crop's
+//     rows are such, since a strip costs a set-up and a load latency per row:
+//     48 photos of 1556 x 1037 to 316 x 316 take 25.0 us in 2 strips of 160
+//     and 29.4 in 3 of 128, 17 of 720 x 660 to 600 x 600 17.0 in 3 of 200
+//     and 21.2 in 5 of 128. Rows of whole 256-byte fp16 lines stay in strips of 128 if
+//     equal widths would cut their lines: 32 frames of 720p to 640 x 640 take
+//     37.0 us in 5 strips of 128, 40.7 in 3 of 216 (61 on the register-gather
+//     kernel); 448 x 448 to 640 x 640 in float 17.6 and 24.7.
+// More strips than that (long source spans) have equal widths.
+void plan_strips(int Cw, bool rgb, int least, int *strips, int *strip_w)
 {
-    const int halves = (Cw + 127) / 128;
-    const int width = Cw <= smol::kStripCols ? Cw : halves % 2 ? 128 : smol::kStripCols;
+    const int halves = (Cw + 127) / 128, fewest = (halves + 1) / 2;
+    int width = halves % 2 ? 128 : smol::kStripCols;
+    if (rgb && (fewest > 2 || halves % 2)) {
+        const int unit = Cw % 32 == 0 ? 32 : 4;
+        const int even = ((Cw + fewest - 1) / fewest + unit - 1) / unit * unit;
+        if (Cw % 128 != 0 || even % 64 == 0)
+            width = even;
+    }
+    if (Cw <= smol::kStripCols)
+        width = Cw;
     *strips = (Cw + width - 1) / width;
     *strip_w = width;
     if (least > *strips) {
@@ -419,12 +434,12 @@ int64_t strip_span(const Desc &d, int64_t whole, int Cw, int cols)
 // span, or 0 if strips of kStripMinCols columns do not fit either. `whole`:
 // the crop's widest span; cols_of(d): the crop's span of one image.
 template <class Whole>
-int64_t fit_strips(const std::vector<Desc> &descs, int Cw, int64_t whole, int64_t max_span,
-                   Whole span_of, BatchArgs *a)
+int64_t fit_strips(const std::vector<Desc> &descs, int Cw, bool rgb, int64_t whole,
+                   int64_t max_span, Whole span_of, BatchArgs *a)
 {
     int least = 1;
     for (;; ++least) {
-        plan_strips(Cw, least, &a->strips, &a->strip_w);
+        plan_strips(Cw, rgb, least, &a->strips, &a->strip_w);
         int64_t span = a->strips == 1 ? whole : 0;
         if (a->strips > 1)
             for (const Desc &d : descs)
@@ -982,7 +997,7 @@ static int rgb_batch(const uint8_t *src, int64_t src_bytes, const int64_t *offse
         int64_t strip_cols = 0;
         if (strips_ok && (forced == smol::PATH_ROWS ||
                           (forced == smol::PATH_AUTO && any_safe && runs_ok)))
-            strip_cols = fit_strips(descs, p->crop_w, max_span / 3,
+            strip_cols = fit_strips(descs, p->crop_w, true, max_span / 3,
                                     (1024 * smol::kRowsMaxGroups - 32) / 3,
                                     [](const Desc &d) { return (int64_t)d.span / 3; }, &a);
         if (strip_cols > 0) {
@@ -1199,7 +1214,7 @@ static int yuv_batch(const uint8_t *src, int64_t src_bytes, const int64_t *y_off
     const int64_t max_strip = max_cspan + 32 <= 1024 ? 2048 - 32 : 2 * (1024 - 32 - 2);
     const int64_t yspan =
         strips_ok && (forced == smol::PATH_ROWS || forced == smol::PATH_AUTO)
-            ? fit_strips(descs, p->crop_w, max_yspan, max_strip,
+            ? fit_strips(descs, p->crop_w, false, max_yspan, max_strip,
                          [](const Desc &d) { return (int64_t)d.span; }, &a)
             : 0;
     if (yspan > 0) {

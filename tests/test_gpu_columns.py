@@ -82,7 +82,7 @@ def test_long_walks(crop, dtype):
     assert _exact(wl, workgroups_per_cu=1)["path"] == smol.PATH_ROWS
 
 
-@pytest.mark.parametrize("width", [257, 300, 384, 385, 513, 640, 701])
+@pytest.mark.parametrize("width", [257, 300, 352, 384, 385, 513, 600, 640, 701, 704, 833])
 @pytest.mark.parametrize("layout", [NCHW, NHWC])
 @pytest.mark.parametrize("dtype", [F32, F16, U8])
 def test_wide_crops(width, layout, dtype):
