@@ -429,9 +429,12 @@ def load_traffic(config: str) -> dict | None:
     if not rec:
         return None
     h = hashlib.sha256()
-    for rel in rec.get("sources", []):
-        with open(os.path.join(ROOT, rel), "rb") as f:
-            h.update(f.read())
+    try:
+        for rel in rec.get("sources", []):
+            with open(os.path.join(ROOT, rel), "rb") as f:
+                h.update(f.read())
+    except OSError:  # a source that is no longer there
+        return None
     if h.hexdigest() != rec.get("sources_sha256"):
         return None
     return rec
