@@ -1,5 +1,5 @@
-// smol_rows_rgb.h -- the RGB row-streaming kernel (rgb_rows_kernel) and the
-// choice of its instance for a plan. The smol_rows_rgb_*.hip files instantiate
+// smol_rows_rgb.h -- the RGB row-streaming kernels (rgb_stride_kernel,
+// rgb_range_kernel) and the
 // its parts.
 #pragma once
 
