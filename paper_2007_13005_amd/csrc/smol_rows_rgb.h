@@ -1,6 +1,6 @@
 // smol_rows_rgb.h -- the RGB row-streaming kernels (rgb_stride_kernel,
-// rgb_range_kernel) and the
-// its parts.
+// rgb_range_kernel) and the choice of their instance for a plan. The
+// smol_rows_rgb_*.hip files instantiate their parts.
 #pragma once
 
 #include "smol_rows.h"
