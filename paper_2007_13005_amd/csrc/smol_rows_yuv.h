@@ -598,8 +598,10 @@ yuv_rows_kernel(BatchArgs a)
                     (long long)strip_start(a, strip) * (NHWC ? 3 : 1) * kEsz;
     const long long owrap = NHWC ? 0 : 2 * plane;
 
+    // The columns' taps depend on the region's width, resized width and crop
+    // offset, and their chroma on its place in the frame and the frame's width.
     YuvCols<J> cols;
-    int cW, cWr, cleft;
+    int cW, cWr, cleft, crx, cfw;
     {
         const YuvImg g = yuv_img(a, c_img, strip);
         if (!a.table && a.wpg > 1)
@@ -610,6 +612,8 @@ yuv_rows_kernel(BatchArgs a)
         cW = g.W;
         cWr = g.Wr;
         cleft = g.left;
+        crx = g.rx;
+        cfw = g.fw;
     }
     const NormK nk = norm_consts(a);
     const uint32_t lds0 = lds_addr(lds);
@@ -641,10 +645,12 @@ yuv_rows_kernel(BatchArgs a)
             ++c_img;
             orow += owrap;
             const YuvImg g = yuv_img(a, c_img, strip);
-            if (g.W != cW || g.Wr != cWr || g.left != cleft) {
+            if (g.W != cW || g.Wr != cWr || g.left != cleft || g.rx != crx || g.fw != cfw) {
                 cW = g.W;
                 cWr = g.Wr;
                 cleft = g.left;
+                crx = g.rx;
+                cfw = g.fw;
                 yuv_cols<J, QUADS>(cols, g, a.strip_w, lane, a.siting);
             }
         }

@@ -114,3 +114,37 @@ def test_yuv_uniform_strips():
     table."""
     wl = _yuv([(2600, 60)] * 6, (64, 250), F16, NCHW, smol.CHROMA_LEFT)
     assert _exact(wl)["path"] == smol.PATH_ROWS
+
+
+def _pick(sizes, n):
+    return [sizes[i % len(sizes) if i % 7 else 0] for i in range(n)]
+
+
+@pytest.mark.parametrize("siting", [smol.CHROMA_CENTER, smol.CHROMA_LEFT])
+@pytest.mark.parametrize("layout", [NCHW, NHWC])
+@pytest.mark.parametrize("crop,sizes", [((64, 72), [(40, 30), (41, 30), (90, 65), (23, 91)]),
+                                        ((3, 131), [(300, 9), (301, 8), (299, 20)]),
+                                        ((40, 224), [(2101, 20), (2100, 21)])],
+                         ids=["many-rows", "many-images", "strips"])
+def test_yuv_long_walks(crop, sizes, layout, siting):
+    """256 waves, each walking many rows (past 64, the rows prepared at once)
+    over several frames of different sizes."""
+    wl = _yuv(_pick(sizes, 17000 // crop[0]), crop, F16, layout, siting)
+    plan = _exact(wl, workgroups_per_cu=1)
+    assert plan["path"] == smol.PATH_ROWS and plan["work_items"] > 64 * plan["grid"]
+
+
+@pytest.mark.parametrize("siting", [smol.CHROMA_CENTER, smol.CHROMA_LEFT])
+@pytest.mark.parametrize("crop", [(16, 72), (16, 200)])
+def test_yuv_equal_rois_walk(crop, siting):
+    """Regions of one size at any place of frames of two widths, many rows per
+    wave: the chroma columns a luma column reads depend on the region's place
+    in its frame and on the frame's width, not on the region's size alone."""
+    rng = np.random.default_rng(8)
+    n = 400
+    sizes = [(97, 40) if i % 3 else (64, 40) for i in range(n)]
+    wl = _yuv(sizes, crop, F32, NCHW, siting)
+    x = [int(rng.integers(0, w - 33 + 1)) if i % 5 else w - 33 for i, (w, _) in enumerate(sizes)]
+    wl.rois = np.array([(x[i], int(rng.integers(0, 20)), 33, 20) for i in range(n)], np.int32)
+    plan = _exact(wl, workgroups_per_cu=1)
+    assert plan["path"] == smol.PATH_ROWS and plan["work_items"] > 8 * plan["grid"]
