@@ -372,7 +372,8 @@ int smol_image_geometry_ex(int32_t width, int32_t height, int32_t yuv420, const 
  *   exact       1: the row-streaming kernels form the normalisation as the
  *               correctly rounded quotient (v - mean) / std and round to
  *               fp16 from that fp32 value, bit-identical to a scalar fp32
- *               evaluation of the definition (the other kernels always do);
+ *               evaluation of the definition (the other kernels always do, and
+ *               calls past the limits of path 4 that run in column strips);
  *               0 (default): they multiply v - mean by RN(1/std), at most
  *               one fp32 ulp from the quotient, and may round that product
  *               to fp16 directly (within one fp16 ulp). Every interpolation

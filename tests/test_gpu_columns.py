@@ -148,3 +148,18 @@ def test_yuv_equal_rois_walk(crop, siting):
     wl.rois = np.array([(x[i], int(rng.integers(0, 20)), 33, 20) for i in range(n)], np.int32)
     plan = _exact(wl, workgroups_per_cu=1)
     assert plan["path"] == smol.PATH_ROWS and plan["work_items"] > 8 * plan["grid"]
+
+
+@pytest.mark.parametrize("dtype", [F32, F16])
+@pytest.mark.parametrize("layout", [NCHW, NHWC])
+@pytest.mark.parametrize("kind,width,crop_w", [("rgb", 700, 600), ("rgb", 300, 513),
+                                               ("rgb", 3840, 224), ("rgb", 1300, 1024),
+                                               ("yuv", 700, 600), ("yuv", 2600, 224)])
+def test_past_the_row_limits_exact_by_default(kind, width, crop_w, layout, dtype):
+    """Crops past 512 columns and spans past one staged row are the oracle's
+    bit for bit without the exact knob, on whichever kernel they run."""
+    sizes, crop = [(width, 40), (width - 1, 33)], (48, crop_w)
+    wl = (_rgb(sizes, crop, dtype, layout) if kind == "rgb" else
+          _yuv(sizes, crop, dtype, layout, smol.CHROMA_CENTER))
+    bits = {F32: np.uint32, F16: np.uint16}[dtype]
+    np.testing.assert_array_equal(run_gpu(wl).view(bits), run_oracle(wl).view(bits))
