@@ -432,21 +432,32 @@ int64_t strip_span(const Desc &d, int64_t whole, int Cw, int cols)
 // Strips for a batch whose strips may span up to max_span source columns:
 // the fewest that fit, in a.strips and a.strip_w; returns the widest strip's
 // span, or 0 if strips of kStripMinCols columns do not fit either. `whole`:
-// the crop's widest span; cols_of(d): the crop's span of one image.
-template <class Whole>
+// the crop's widest span; span_of(d): the crop's span of one image.
+// A few long spans among short ones would put every image into narrow strips, so
+// an RGB batch most of whose spans fit the crop's own strips gets 0 as well (255
+// photos of 400 x 400 and one of 3840 x 2160 to 224 x 224: 103 us in strips, 85 on
+// the register-gather kernel; an I420 batch has only the direct kernel to go to: 63
+// frames of 640 x 480 and one of 3840 x 2160 26 us in strips, 84 there).
+template <class Span>
 int64_t fit_strips(const std::vector<Desc> &descs, int Cw, bool rgb, int64_t whole,
-                   int64_t max_span, Whole span_of, BatchArgs *a)
+                   int64_t max_span, Span span_of, BatchArgs *a)
 {
-    int least = 1;
-    for (;; ++least) {
+    for (int least = 1;; least = std::max(least, a->strips) + 1) {
         plan_strips(Cw, rgb, least, &a->strips, &a->strip_w);
+        if (a->strips > 1 && a->strip_w < smol::kStripMinCols)
+            return 0;
         int64_t span = a->strips == 1 ? whole : 0;
-        if (a->strips > 1)
-            for (const Desc &d : descs)
-                span = std::max(span, strip_span(d, span_of(d), Cw, a->strip_w));
+        size_t past = 0;
+        for (const Desc &d : descs) {
+            const int64_t s = strip_span(d, span_of(d), Cw, a->strip_w);
+            span = std::max(span, s);
+            past += s > max_span ? 1 : 0;
+        }
         if (span <= max_span)
             return span;
-        if (a->strip_w <= smol::kStripMinCols)
+        if (a->strip_w == Cw && Cw <= smol::kStripMinCols)
+            return 0;
+        if (rgb && least == 1 && 2 * past < descs.size())
             return 0;
     }
 }

@@ -86,6 +86,7 @@ constexpr int PATH_YUV_ROWS = 5;
 // strips of at least kStripMinCols columns (RGB frames to 224 x 224 against the
 // register-gather kernel: 32 of 3840 x 2160 20.4 / 26.0 us, 12 of 7680 x 4320 in
 // strips of 56 columns 16.1 / 21.2, 8 of 9600 x 5400 in strips of 48 13.5 / 14.9;
+// narrower strips lose: 32 of 3840 x 2160 to 128 x 128 in strips of 44 18.3 / 17.1;
 // 32 I420 frames of 3840 x 2160 against the direct kernel 17.4 / 35.8). A call of
 // fewer than kStripsMinRows I420 rows is bound by its launch on either kernel and
 // stays on the direct one.

@@ -163,3 +163,21 @@ def test_past_the_row_limits_exact_by_default(kind, width, crop_w, layout, dtype
           _yuv(sizes, crop, dtype, layout, smol.CHROMA_CENTER))
     bits = {F32: np.uint32, F16: np.uint16}[dtype]
     np.testing.assert_array_equal(run_gpu(wl).view(bits), run_oracle(wl).view(bits))
+
+
+@pytest.mark.parametrize("crop_w,path", [(100, smol.PATH_GATHER), (112, smol.PATH_GATHER),
+                                         (128, smol.PATH_GATHER), (160, smol.PATH_ROWS),
+                                         (224, smol.PATH_ROWS)])
+def test_no_strip_below_the_narrowest(crop_w, path):
+    """Spans of 3840 columns need three strips or more: fewer than 48 columns
+    each below a crop of 144."""
+    assert _exact(_rgb([(3840, 24)] * 2, (8, crop_w), F16, NCHW))["path"] == path
+
+
+@pytest.mark.parametrize("wide,path", [(1, smol.PATH_GATHER), (3, smol.PATH_GATHER),
+                                       (4, smol.PATH_ROWS), (7, smol.PATH_ROWS)])
+def test_few_long_spans(wide, path):
+    """Images of long spans among images that fit their crop's own strips: strips
+    for all only where at least half of them need it."""
+    wl = _rgb([(3000, 20)] * wide + [(400, 30)] * (8 - wide), (16, 224), F16, NCHW)
+    assert _exact(wl)["path"] == path
