@@ -644,7 +644,7 @@ __device__ __forceinline__ void pack_pair(RowOut<F16, J> &out, int j, const floa
 // loads. uint8 output is stored ordinarily: it is small, and the
 // low-resolution op reads it back at once (step 2 of 256 images: 24.3 us, 29.7
 // after nontemporal stores).
-template <int N, bool NT = true>
+template <int N, bool NT>
 __device__ __forceinline__ void store_words(uint8_t *dst,
                                             uint32_t __attribute__((ext_vector_type(N))) v)
 {
@@ -655,19 +655,23 @@ __device__ __forceinline__ void store_words(uint8_t *dst,
         *(Unaligned *)dst = v;
 }
 
+template <bool NT>
 __device__ __forceinline__ void store_half(uint8_t *dst, uint32_t v)
 {
     typedef uint16_t __attribute__((aligned(1))) Unaligned;
-    *(Unaligned *)dst = (uint16_t)v;
+    if (NT)
+        __builtin_nontemporal_store((uint16_t)v, (Unaligned *)dst);
+    else
+        *(Unaligned *)dst = (uint16_t)v;
 }
 
-template <int F16, int J, int ONE>
+template <int F16, int J, int ONE, bool QUADS, bool NT>
 __device__ __forceinline__ void store_row(uint8_t *orow, long long plane, int cols, int lane,
                                           const RowOut<F16, J> &out, int nhwc)
 {
     static_assert(J == 1 || J == 2, "one or two column pairs per lane");
     constexpr int kEsz = F16 == 2 ? 1 : F16 ? 2 : 4;
-    const int c = pair_col<J, true>(lane, 0, cols);
+    constexpr bool FOUR = QUADS && J == 2;  // the lane's columns lie side by side
     if constexpr (ONE) {
 #pragma unroll
         for (int ch = 0; ch < 3; ++ch) {
@@ -682,27 +686,30 @@ __device__ __forceinline__ void store_row(uint8_t *orow, long long plane, int co
         return;
     }
     if (!nhwc) {
-        const uint32_t lo = (uint32_t)c * kEsz;
 #pragma unroll
-        for (int ch = 0; ch < 3; ++ch) {
-            uint8_t *dst = orow + ch * plane + lo;
-            if constexpr (F16 == 2 && J == 1)
-                store_half(dst, out.word(ch, 0));
-            else if constexpr (F16 == 2)
-                store_words<1, false>(dst, (out.word(ch, 0) & 0xffffu) | (out.word(ch, J - 1) << 16));
-            else if constexpr (F16 && J == 1)
-                store_words<1>(dst, out.word(ch, 0));
-            else if constexpr (F16 || J == 1)
-                store_words<2>(dst, u32x2{out.word(ch, 0), F16 ? out.word(ch, J - 1)
-                                                               : out.word(ch, 0, F16 ? 0 : 1)});
-            else
-                store_words<4>(dst, u32x4{out.word(ch, 0), out.word(ch, 0, F16 ? 0 : 1),
-                                          out.word(ch, J - 1),
-                                          out.word(ch, J - 1, F16 ? 0 : 1)});
+        for (int j = 0; j < (FOUR ? 1 : J); ++j) {
+            const uint32_t lo = (uint32_t)pair_col<J, QUADS>(lane, j, cols) * kEsz;
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) {
+                uint8_t *dst = orow + ch * plane + lo;
+                if constexpr (F16 == 2 && !FOUR)
+                    store_half<NT>(dst, out.word(ch, j));
+                else if constexpr (F16 == 2)
+                    store_words<1, NT>(dst, (out.word(ch, 0) & 0xffffu) |
+                                                   (out.word(ch, J - 1) << 16));
+                else if constexpr (F16 && !FOUR)
+                    store_words<1, NT>(dst, out.word(ch, j));
+                else if constexpr (F16)
+                    store_words<2, NT>(dst, u32x2{out.word(ch, 0), out.word(ch, J - 1)});
+                else if constexpr (!FOUR)
+                    store_words<2, NT>(dst, u32x2{out.word(ch, j), out.word(ch, j, 1)});
+                else
+                    store_words<4, NT>(dst, u32x4{out.word(ch, 0), out.word(ch, 0, 1),
+                                              out.word(ch, J - 1), out.word(ch, J - 1, 1)});
+            }
         }
         return;
     }
-    uint8_t *dst = orow + 3u * (uint32_t)c * kEsz;
     typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
     if constexpr (F16 == 2) {
         // a pair is r0 g0 b0 r1 g1 b1, the bytes of a word being pixels c, c + 1
@@ -713,12 +720,17 @@ __device__ __forceinline__ void store_row(uint8_t *orow, long long plane, int co
             lo[j] = (r & 0xffu) | (g & 0xffu) << 8 | (b & 0xffu) << 16 | (r & 0xff00u) << 16;
             hi[j] = (g >> 8 & 0xffu) | (b & 0xff00u);
         }
-        if constexpr (J == 1) {
-            store_words<1, false>(dst, lo[0]);
-            store_half(dst + 4, hi[0]);
+        if constexpr (!FOUR) {
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                uint8_t *dj = orow + 3u * (uint32_t)pair_col<J, QUADS>(lane, j, cols);
+                store_words<1, NT>(dj, lo[j]);
+                store_half<NT>(dj + 4, hi[j]);
+            }
         } else {
-            store_words<3, false>(dst, u32x3{lo[0], hi[0] | lo[J - 1] << 16,
-                                             lo[J - 1] >> 16 | hi[J - 1] << 16});
+            store_words<3, NT>(orow + 3u * (uint32_t)pair_col<J, true>(lane, 0, cols),
+                                  u32x3{lo[0], hi[0] | lo[J - 1] << 16,
+                                        lo[J - 1] >> 16 | hi[J - 1] << 16});
         }
     } else {
 #pragma unroll
@@ -727,13 +739,13 @@ __device__ __forceinline__ void store_row(uint8_t *orow, long long plane, int co
             uint8_t *dj = orow + 3u * (uint32_t)pair_col<J, false>(lane, j, cols) * kEsz;
             if constexpr (F16) {
                 const uint32_t w0 = out.word(0, j), w1 = out.word(1, j), w2 = out.word(2, j);
-                store_words<3>(dj, u32x3{(w0 & 0xffffu) | (w1 << 16),
+                store_words<3, NT>(dj, u32x3{(w0 & 0xffffu) | (w1 << 16),
                                          (w2 & 0xffffu) | (w0 & 0xffff0000u),
                                          (w1 >> 16) | (w2 & 0xffff0000u)});
             } else {
-                store_words<2>(dj, u32x2{out.word(0, j), out.word(1, j)});
-                store_words<2>(dj + 8, u32x2{out.word(2, j), out.word(0, j, 1)});
-                store_words<2>(dj + 16, u32x2{out.word(1, j, 1), out.word(2, j, 1)});
+                store_words<2, NT>(dj, u32x2{out.word(0, j), out.word(1, j)});
+                store_words<2, NT>(dj + 8, u32x2{out.word(2, j), out.word(0, j, 1)});
+                store_words<2, NT>(dj + 16, u32x2{out.word(1, j, 1), out.word(2, j, 1)});
             }
         }
     }

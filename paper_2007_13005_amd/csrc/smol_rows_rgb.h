@@ -100,7 +100,7 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_stride_kernel(
         advance();                                                                            \
         compute();                                                                            \
         write_rows<G>(lds, NXT, lane);                                                        \
-        store_row<F16, J, ONE>(orow, plane, a.strip_w, lane, out, NHWC);                       \
+        store_row<F16, J, ONE, QUADS, true>(orow, plane, a.strip_w, lane, out, NHWC);         \
         csh0 = NXT.sh0;                                                                       \
         csh1 = NXT.sh1;                                                                       \
         cwy = NXT.wy;                                                                         \
@@ -140,7 +140,7 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_stride_kernel(
     }
 #undef SMOL_ROWS_STEP
     compute();
-    store_row<F16, J, ONE>(orow, plane, a.strip_w, lane, out, NHWC);
+    store_row<F16, J, ONE, QUADS, true>(orow, plane, a.strip_w, lane, out, NHWC);
 }
 
 // Contiguous walk: wave w takes a range of consecutive output rows. The wave's
@@ -167,8 +167,12 @@ template <int F16, int J, int EXACT, int G, int FORM>
 __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_range_kernel(BatchArgs a)
 {
     constexpr int NHWC = FORM & kFormNhwc, ONE = (FORM & kFormOne) ? 1 : 0;
-    constexpr bool QUADS = !NHWC || F16 == 2;
+    // Long staged rows are large shrinks, whose lanes' taps lie far apart (four
+    // columns side by side at a shrink by 5.3: 16 words, 4 of the 64 LDS banks;
+    // pairs: 8 words and 8 banks).
+    constexpr bool QUADS = (!NHWC || F16 == 2) && G <= 2;
     constexpr bool LINES = (FORM & kFormLines) != 0;
+    constexpr bool NT = F16 != 2 || G >= 4;
     static_assert(!LINES || (F16 == 1 && !NHWC && !ONE), "whole lines: fp16 NCHW");
     constexpr int kEsz = F16 == 2 ? 1 : F16 ? 2 : 4;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_all[];
@@ -245,12 +249,11 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_range_kernel(B
             ((u32x4 *)(lds + 1024 * G))[64 * g + lane] = st.c1[g];
         }
     };
-    // The first two rows are requested before the column taps and the rest of
-    // the set-up are computed.
-    Chunks first, ahead;
-    load_next(first);
-    RowS cur = nxt;
+    // The first row is requested before the column taps and the rest of the
+    // set-up are computed.
+    Chunks ahead;
     load_next(ahead);
+    RowS cur = nxt;
 
     // bytes between an image's output rows: Cw elements per plane (NCHW) or
     // 3 Cw (NHWC); a wrap to the next image skips the rest of the image.
@@ -305,18 +308,23 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_range_kernel(B
     uint8_t *const ring = lds + 2048 * G;
     uint32_t pos = LINES ? (uint32_t)(uintptr_t)orow & 127u : 0u;  // the row's first byte
     uint32_t done = pos;                                          // bytes stored so far
-    const uint32_t lane_out = LINES ? 2u * (uint32_t)pair_col<J, true>(lane, 0, a.strip_w) : 0u;
+    const uint32_t lane_out = LINES ? 2u * (uint32_t)pair_col<J, QUADS>(lane, 0, a.strip_w) : 0u;
+    const uint32_t lane_out1 =
+        LINES ? 2u * (uint32_t)pair_col<J, QUADS>(lane, J - 1, a.strip_w) : 0u;
     // store the row; `last`: the wave's last row
     auto store = [&](bool last) {
         if constexpr (!LINES) {
-            store_row<F16, J, ONE>(orow, plane, a.strip_w, lane, out, NHWC);
+            store_row<F16, J, ONE, QUADS, NT>(orow, plane, a.strip_w, lane, out, NHWC);
         } else {
             const uint32_t wo = (pos + lane_out) & (kLineRing - 1);
+            const uint32_t w1 = (pos + lane_out1) & (kLineRing - 1);
 #pragma unroll
             for (int ch = 0; ch < 3; ++ch) {
-                if constexpr (J == 1)
+                if constexpr (J == 1 || !QUADS) {
                     *(uint32_t *)(ring + ch * kLineRing + wo) = out.word(ch, 0);
-                else
+                    if constexpr (J == 2)
+                        *(uint32_t *)(ring + ch * kLineRing + w1) = out.word(ch, J - 1);
+                } else
                     *(u32x2 *)(ring + ch * kLineRing + wo) = u32x2{out.word(ch, 0), out.word(ch, J - 1)};
             }
             const uint32_t end = pos + (uint32_t)rb;
@@ -327,24 +335,17 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_range_kernel(B
             uint8_t *dst = orow - (pos - done);
 #pragma unroll
             for (int ch = 0; ch < 3; ++ch)
-                store_words<4>(dst + ch * plane + off, *(const u32x4 *)(ring + ch * kLineRing + ro));
+                store_words<4, true>(dst + ch * plane + off, *(const u32x4 *)(ring + ch * kLineRing + ro));
             done = to;
             pos = end;
         }
     };
-    // The loads of row k + 2 go out before the stores of row k: loads and
-    // stores complete in order, so the wait for row k + 2, one step later,
-    // then leaves row k's stores outstanding. The count of the loop's wait
-    // holds for its first turn too because row 1 has arrived before the loop.
-    stage(first);
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-        asm volatile("" : "+v"(ahead.c0[g]), "+v"(ahead.c1[g]));
+    stage(ahead);
     for (int left = n_rows - 1; left > 0; --left) {
+        load_next(ahead);
         compute(cur);
         stage(ahead);
         cur = nxt;
-        load_next(ahead);
         store(false);
         orow += rowb;
         if (++c_rr == Ch) {

@@ -638,7 +638,7 @@ yuv_rows_kernel(BatchArgs a)
         load_next();
         yuv_compute_row<F16, J, EXACT, GL>(nk, lds0, csh, cwy, cfy0, cfy1, cols, out);
         stage();
-        store_row<F16, J, ONE>(orow, plane, a.strip_w, lane, out, NHWC);
+        store_row<F16, J, ONE, QUADS, true>(orow, plane, a.strip_w, lane, out, NHWC);
         orow += rowb;
         if (++c_rr == Ch) {
             c_rr = 0;
@@ -656,7 +656,7 @@ yuv_rows_kernel(BatchArgs a)
         }
     }
     yuv_compute_row<F16, J, EXACT, GL>(nk, lds0, csh, cwy, cfy0, cfy1, cols, out);
-    store_row<F16, J, ONE>(orow, plane, a.strip_w, lane, out, NHWC);
+    store_row<F16, J, ONE, QUADS, true>(orow, plane, a.strip_w, lane, out, NHWC);
 }
 
 // a.row_groups: KiB per staged luma row, 1 or 2

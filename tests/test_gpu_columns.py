@@ -181,3 +181,15 @@ def test_few_long_spans(wide, path):
     for all only where at least half of them need it."""
     wl = _rgb([(3000, 20)] * wide + [(400, 30)] * (8 - wide), (16, 224), F16, NCHW)
     assert _exact(wl)["path"] == path
+
+
+@pytest.mark.parametrize("width", [1, 3, 128, 130, 131, 224, 256])
+@pytest.mark.parametrize("layout", [NCHW, NHWC])
+@pytest.mark.parametrize("dtype", [F32, F16, U8])
+def test_long_rows_in_ranges(width, layout, dtype):
+    """Ragged batches of long staged rows (past 2 KiB), one row and many per
+    wave: pairs of columns per lane instead of four side by side."""
+    sizes = [(1300, 40), (1299, 33), (900, 70)]
+    wl = _rgb(sizes, (64, width), dtype, layout)
+    assert _exact(wl)["path"] == smol.PATH_ROWS
+    assert _exact(_rgb(sizes * 30, (64, width), dtype, layout), workgroups_per_cu=1)["grid"] == 256
