@@ -389,28 +389,23 @@ struct Plan {
 // last column and overlaps its neighbour.
 //   I420: 256 columns (two column pairs per lane) or, where that leaves an odd
 //     number of 128-column halves, 128 (one pair per lane).
-//   RGB, 385-512 columns: 256. Elsewhere the fewest strips of up to 256
-//     columns in equal widths, of whole 128-byte float lines where the crop's
-//     rows are such, since a strip costs a set-up and a load latency per row:
-//     48 photos of 1556 x 1037 to 316 x 316 take 25.0 us in 2 strips of 160
-//     and 29.4 in 3 of 128, 17 of 720 x 660 to 600 x 600 17.0 in 3 of 200
-//     and 21.2 in 5 of 128. Rows of whole 256-byte fp16 lines stay in strips of 128 if
-//     equal widths would cut their lines: 32 frames of 720p to 640 x 640 take
-//     37.0 us in 5 strips of 128, 40.7 in 3 of 216 (61 on the register-gather
-//     kernel); 448 x 448 to 640 x 640 in float 17.6 and 24.7.
+//   RGB: the fewest strips of up to 256 columns in equal widths, of whole
+//     128-byte float lines where the crop's rows are such, since a strip costs a
+//     set-up and a load latency per row, and what overlaps is computed and
+//     stored twice: 48 photos of 1556 x 1037 to 316 x 316 take 25.0 us in 2
+//     strips of 160 and 29.4 in 3 of 128, 128 of 640 x 480 to 448 x 448 62.7 in 2
+//     of 224 and 66.4 in 2 of 256 (float 91.2 and 104.3), 16 of 720p to 896 x
+//     512 22.0 in 4 of 224 and 23.3 in 7 of 128, 32 of 720p to 640 x 640 40.4
+//     in 3 of 224 and 40.8 in 5 of 128.
 // More strips than that (long source spans) have equal widths.
 void plan_strips(int Cw, bool rgb, int least, int *strips, int *strip_w)
 {
     const int halves = (Cw + 127) / 128, fewest = (halves + 1) / 2;
-    int width = halves % 2 ? 128 : smol::kStripCols;
-    if (rgb && (fewest > 2 || halves % 2)) {
-        const int unit = Cw % 32 == 0 ? 32 : 4;
-        const int even = ((Cw + fewest - 1) / fewest + unit - 1) / unit * unit;
-        if (Cw % 128 != 0 || even % 64 == 0)
-            width = even;
-    }
-    if (Cw <= smol::kStripCols)
-        width = Cw;
+    const int unit = Cw % 32 == 0 ? 32 : 4;
+    const int width = Cw <= smol::kStripCols ? Cw
+                      : rgb          ? ((Cw + fewest - 1) / fewest + unit - 1) / unit * unit
+                      : halves % 2   ? 128
+                                     : smol::kStripCols;
     *strips = (Cw + width - 1) / width;
     *strip_w = width;
     if (least > *strips) {

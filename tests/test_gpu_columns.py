@@ -193,3 +193,11 @@ def test_long_rows_in_ranges(width, layout, dtype):
     wl = _rgb(sizes, (64, width), dtype, layout)
     assert _exact(wl)["path"] == smol.PATH_ROWS
     assert _exact(_rgb(sizes * 30, (64, width), dtype, layout), workgroups_per_cu=1)["grid"] == 256
+
+
+@pytest.mark.parametrize("crop_w,strips", [(300, 2), (384, 2), (448, 2), (512, 2), (600, 3),
+                                           (640, 3), (768, 3), (896, 4), (1024, 4)])
+def test_rgb_strip_counts(crop_w, strips):
+    """RGB crops run in the fewest strips of up to 256 columns."""
+    wl = _rgb([(640, 40), (633, 41)], (16, crop_w), F16, NCHW)
+    assert _exact(wl)["work_items"] == 2 * 16 * strips
