@@ -368,7 +368,7 @@ int smol_image_geometry_ex(int32_t width, int32_t height, int32_t yuv420, const 
  *               or 4 independent waves, the cap counts waves; by default as
  *               many as can be resident (row streaming with 4 KiB staged
  *               rows: 8 waves); for block decoding (smol_jpeg.h) the
- *               launch's one-wave workgroups per compute unit (default 128)
+ *               launch's one-wave workgroups per compute unit (default 256)
  *   exact       1: the row-streaming kernels form the normalisation as the
  *               correctly rounded quotient (v - mean) / std and round to
  *               fp16 from that fp32 value, bit-identical to a scalar fp32
@@ -382,7 +382,8 @@ int smol_image_geometry_ex(int32_t width, int32_t height, int32_t yuv420, const 
  *               of output rows; 2 wave q of G takes rows q, q + G, ...
  *               (concurrently running waves stream neighbouring rows);
  *               0 (default): 2 for uniform batches whose staged rows exceed
- *               2 KiB, else 1. I420 waves always take contiguous ranges
+ *               2 KiB, in at most two column strips, else 1. I420 waves
+ *               always take contiguous ranges
  *   upload      how a ragged batch's descriptor table reaches the device:
  *               0 (default) or 3: no copy, the preprocessing kernel reads the
  *               pinned staging slot itself (one launch per call); 1 a DMA

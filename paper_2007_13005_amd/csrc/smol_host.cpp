@@ -564,11 +564,14 @@ int run_batch(const std::vector<Desc> &descs, size_t first, size_t count, int no
         // waves then stream neighbouring rows), contiguous ranges otherwise.
         // 64 frames of 1080p from memory, inputs past the 256 MB cache: 21.8
         // us interleaved, 24.5 in ranges (20.9 in ranges with half of them
-        // cached). (Set before the occupancy query: the two walks are
-        // different kernels.)
+        // cached). Spans in three or more strips, ranges: 32 frames of 4K to 256
+        // x 256 33.5 us, 36.0 interleaved; 16 of 5120 x 2880 to 384 x 384 31.5 and
+        // 33.4 (in two strips, 64 of 1080p to 256 x 256 41.3 and 36.7). (Set before
+        // the occupancy query: the two walks are different kernels.)
         const int order = g_row_order.load();
         a.interleave = pl.path == smol::PATH_ROWS && pl.f16 != SMOL_OUT_U8 &&
-                       (order == 2 || (order == 0 && uniform && a.row_groups >= 4));
+                       (order == 2 || (order == 0 && uniform && a.row_groups >= 4 &&
+                                       a.strips <= 2));
         // Whole-line stores: rows of 16-byte multiples, at least one line
         // long, that are not whole lines themselves, in planes of whole lines.
         const long long rb = 2LL * a.Cw;
