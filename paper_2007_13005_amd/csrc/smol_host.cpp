@@ -457,6 +457,20 @@ int64_t fit_strips(const std::vector<Desc> &descs, int Cw, bool rgb, int64_t who
     }
 }
 
+// The crop in one strip (the caller has checked its span); returns the span.
+int64_t one_strip_of(int Cw, int64_t span, BatchArgs *a)
+{
+    a->strips = 1;
+    a->strip_w = Cw;
+    return span;
+}
+
+// Column pairs per lane for strips of a.strip_w columns.
+int column_pairs(const BatchArgs &a)
+{
+    return a.strip_w <= 128 ? 1 : a.strip_w <= smol::kStripCols ? 2 : smol::kRowsWidePairs;
+}
+
 size_t align16(size_t v) { return (v + 15) & ~(size_t)15; }
 
 // LDS layout of the RGB kernel: two buffers per workgroup, each
@@ -576,7 +590,7 @@ int run_batch(const std::vector<Desc> &descs, size_t first, size_t count, int no
         // long, that are not whole lines themselves, in planes of whole lines.
         const long long rb = 2LL * a.Cw;
         a.lines = pl.path == smol::PATH_ROWS && pl.f16 == SMOL_OUT_F16 && !a.interleave &&
-                  !a.nhwc && a.strips == 1 && rb % 16 == 0 && rb >= 128 && rb % 128 != 0 &&
+                  !a.nhwc && a.Cw <= smol::kStripCols && a.strips == 1 && rb % 16 == 0 && rb >= 128 && rb % 128 != 0 &&
                   rb * a.Ch % 128 == 0 && ((uintptr_t)a.out & 127) == 0;
         if (a.lines)
             pl.lds_bytes += 3 * smol::kLineRing;
@@ -1003,10 +1017,22 @@ static int rgb_batch(const uint8_t *src, int64_t src_bytes, const int64_t *offse
         const bool strips_ok = rows_ok || (have_dev && forced == smol::PATH_AUTO &&
                                            g_lds_budget.load() == 0 &&
                                            p->crop_w <= smol::kStripsMaxCols);
+        // Crops past kStripCols columns in one strip, four column pairs per lane,
+        // where strips are slower: the strided walk of long rows (32 frames of 720p
+        // to 300 x 300 20.1 us and 21.7 in strips, to 448 x 448 25.2 and 26.6) and
+        // interleaved float rows (128 of 640 x 480 to 448 x 448 103 and 108). (The
+        // kernels have these instances only: kRowsWidePairs.)
+        int64_t stride = 0;
+        const int order = g_row_order.load();
+        const bool one_strip =
+            rows_ok && p->crop_w > smol::kStripCols &&
+            (groups > 2 ? order != 1 && f16 != SMOL_OUT_U8 &&
+                              (order == 2 || is_uniform(descs, 0, (size_t)n, 1, &stride))
+                        : order != 2 && f16 == SMOL_OUT_F32 && a.nhwc);
         int64_t strip_cols = 0;
         if (strips_ok && (forced == smol::PATH_ROWS ||
                           (forced == smol::PATH_AUTO && any_safe && runs_ok)))
-            strip_cols = fit_strips(descs, p->crop_w, true, max_span / 3,
+            strip_cols = one_strip ? one_strip_of(p->crop_w, max_span / 3, &a) : fit_strips(descs, p->crop_w, true, max_span / 3,
                                     (1024 * smol::kRowsMaxGroups - 32) / 3,
                                     [](const Desc &d) { return (int64_t)d.span / 3; }, &a);
         if (strip_cols > 0) {
@@ -1017,7 +1043,7 @@ static int rgb_batch(const uint8_t *src, int64_t src_bytes, const int64_t *offse
             // (as the other kernels form it; no slower: 32 frames of 4K to 224
             // x 224 19.5 us either way, of 720p to 640 x 640 39.6)
             a.exact = a.exact || !rows_ok;
-            a.col_iters = a.strip_w <= 128 ? 1 : 2;
+            a.col_iters = column_pairs(a);
             a.row_groups = (int)(lds_bytes / 2048);
             // Prefetch depth (band_rows 1 or 2 forces it): long staged rows
             // keep one row in flight per wave, short ones two.
@@ -1225,15 +1251,19 @@ static int yuv_batch(const uint8_t *src, int64_t src_bytes, const int64_t *y_off
                     "than %d columns, the luma span exceeds 2016 bytes or the chroma span 992",
                     smol::kRowsMaxCols);
     const int64_t max_strip = max_cspan + 32 <= 1024 ? 2048 - 32 : 2 * (1024 - 32 - 2);
+    // (float crops past kStripCols columns in one strip, four column pairs per lane:
+    // 128 frames of 640 x 480 to 512 x 512 take 133.5 us so and 143.7 in strips, to
+    // 300 x 300 76.6 and 89.0; fp16 ones 95.6 and 84.5 to 384 x 384)
+    const bool one_strip = rows_ok && p->crop_w > smol::kStripCols && f16 == SMOL_OUT_F32;
     const int64_t yspan =
-        strips_ok && (forced == smol::PATH_ROWS || forced == smol::PATH_AUTO)
-            ? fit_strips(descs, p->crop_w, false, max_yspan, max_strip,
-                         [](const Desc &d) { return (int64_t)d.span; }, &a)
-            : 0;
+        !strips_ok || (forced != smol::PATH_ROWS && forced != smol::PATH_AUTO) ? 0
+        : one_strip ? one_strip_of(p->crop_w, max_yspan, &a)
+                    : fit_strips(descs, p->crop_w, false, max_yspan, max_strip,
+                                 [](const Desc &d) { return (int64_t)d.span; }, &a);
     if (yspan > 0) {
         // (as for RGB; 32 frames of 4K 17.1 and 17.2 us)
         a.exact = a.exact || !rows_ok;
-        a.col_iters = a.strip_w <= 128 ? 1 : 2;
+        a.col_iters = column_pairs(a);
         // luma segments of 1 or 2 KiB, six chroma segments of 1 KiB per wave
         a.row_groups = yspan + 32 <= 1024 ? 1 : 2;
         const Plan pr{smol::PATH_YUV_ROWS, 0, (size_t)(2 * a.row_groups + 6) * 1024, 0, f16};

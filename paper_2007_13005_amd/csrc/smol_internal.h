@@ -48,7 +48,7 @@ struct BatchArgs {
     int32_t grid;        // workgroups of a persistent launch (LDS kernels)
     int32_t stage_bytes; // bytes of one of the two LDS buffers of a wave
     int32_t row_groups;  // 1 KiB chunk groups per staged source row (row-streaming kernel)
-    int32_t col_iters;   // column pairs per lane: 1 or 2 (row-streaming kernel)
+    int32_t col_iters;   // column pairs per lane: 1, 2 or kRowsWidePairs (row streaming)
     // Row streaming: the crop's columns are `strips` strips of strip_w (the
     // last one ends at the last column), one per workgroup row of the grid.
     int32_t strips, strip_w;
@@ -92,6 +92,7 @@ constexpr int PATH_YUV_ROWS = 5;
 // stays on the direct one.
 constexpr int kRowsMaxCols = 512;
 constexpr int kStripCols = 256;
+constexpr int kRowsWidePairs = 4;  // column pairs per lane of a strip past kStripCols columns
 constexpr int kStripsMaxCols = 2048;
 constexpr int kStripMinCols = 48;
 constexpr int kStripsMinRows = 64;

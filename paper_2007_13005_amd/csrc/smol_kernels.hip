@@ -876,7 +876,7 @@ const void *yuv_rows_kernel_for(const BatchArgs &a, int f16)
 // 2 J columns (the kernel's yuv_col_table_bytes).
 static size_t yuv_rows_table_lds(const BatchArgs &a, bool uniform)
 {
-    const size_t J = a.col_iters <= 1 ? 1 : 2;
+    const size_t J = (size_t)a.col_iters;
     return uniform && a.wpg > 1 ? 2 * J * 64 * 32 : 0;
 }
 

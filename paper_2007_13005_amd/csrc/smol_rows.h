@@ -669,7 +669,7 @@ template <int F16, int J, int ONE, bool QUADS, bool NT>
 __device__ __forceinline__ void store_row(uint8_t *orow, long long plane, int cols, int lane,
                                           const RowOut<F16, J> &out, int nhwc)
 {
-    static_assert(J == 1 || J == 2, "one or two column pairs per lane");
+    static_assert(!(QUADS && J > 2), "four columns side by side at most");
     constexpr int kEsz = F16 == 2 ? 1 : F16 ? 2 : 4;
     constexpr bool FOUR = QUADS && J == 2;  // the lane's columns lie side by side
     if constexpr (ONE) {

@@ -14,7 +14,7 @@ template <int F16, int J, int EXACT, int G, int P, int FORM>
 __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_stride_kernel(BatchArgs a)
 {
     constexpr int NHWC = FORM & kFormNhwc, ONE = (FORM & kFormOne) ? 1 : 0;
-    constexpr bool QUADS = !NHWC || F16 == 2;
+    constexpr bool QUADS = (!NHWC || F16 == 2) && J <= 2;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_all[];
     int lane;
     long long r0;
@@ -170,7 +170,7 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_range_kernel(B
     // Long staged rows are large shrinks, whose lanes' taps lie far apart (four
     // columns side by side at a shrink by 5.3: 16 words, 4 of the 64 LDS banks;
     // pairs: 8 words and 8 banks).
-    constexpr bool QUADS = (!NHWC || F16 == 2) && G <= 2;
+    constexpr bool QUADS = (!NHWC || F16 == 2) && G <= 2 && J <= 2;
     constexpr bool LINES = (FORM & kFormLines) != 0;
     constexpr bool NT = F16 != 2 || G >= 4;
     static_assert(!LINES || (F16 == 1 && !NHWC && !ONE), "whole lines: fp16 NCHW");
@@ -278,6 +278,10 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_range_kernel(B
     bool swap = false;  // hB holds y0's lerps, hA y1's
     RowOut<F16, J> out;
     auto compute = [&](const RowS &row) {
+        if constexpr (J > 2) {
+            rows_compute<F16, J, EXACT>(nk, lds0 + row.sh0, lds1 + row.sh1, row.wy, cx, cw, out);
+            return;
+        }
         if (row.rel == kRowNew) {
             swap = false;
             rows_horizontal<J>(lds0 + row.sh0, cx, cw, hA);
@@ -384,6 +388,10 @@ const void *rgb_rows_g(const BatchArgs &a)
         if (a.lines)
             return a.col_iters > 1 ? rgb_rows_k<F16, EXACT, G, STRIDE, kFormLines, 2>(a)
                                    : rgb_rows_k<F16, EXACT, G, STRIDE, kFormLines, 1>(a);
+    // (the forms that the host's plan takes to one wide strip)
+    if constexpr (STRIDE ? G == 4 : F16 == 0 && NHWC && G <= 2)
+        if (a.col_iters > 2)
+            return rgb_rows_k<F16, EXACT, G, STRIDE, NHWC, kRowsWidePairs>(a);
     return a.col_iters > 1 ? rgb_rows_k<F16, EXACT, G, STRIDE, NHWC, 2>(a)
            : a.Cw > 1      ? rgb_rows_k<F16, EXACT, G, STRIDE, NHWC, 1>(a)
                            : rgb_rows_k<F16, EXACT, G, STRIDE, NHWC | kFormOne, 1>(a);

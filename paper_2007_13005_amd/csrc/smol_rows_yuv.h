@@ -548,11 +548,11 @@ __device__ __forceinline__ void yuv_compute_row(const NormK &nk, uint32_t slot, 
 // Wave w walks a range of consecutive output rows. FORM: kFormNhwc, kFormOne;
 // GL: chunks per lane of a luma segment (staged luma rows of up to 1 or 2 KiB).
 template <int F16, int J, int EXACT, int FORM, int GL>
-__global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) __attribute__((amdgpu_waves_per_eu(3)))
-yuv_rows_kernel(BatchArgs a)
+__global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup)
+__attribute__((amdgpu_waves_per_eu(J > 2 ? 2 : 3))) yuv_rows_kernel(BatchArgs a)
 {
     constexpr int NHWC = FORM & kFormNhwc, ONE = (FORM & kFormOne) ? 1 : 0;
-    constexpr bool QUADS = !NHWC;
+    constexpr bool QUADS = !NHWC && J <= 2;
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_all[];
     int lane;
     long long r0;
@@ -663,6 +663,9 @@ yuv_rows_kernel(BatchArgs a)
 template <int F16, int EXACT, int NHWC, int GL>
 const void *yuv_rows_g(const BatchArgs &a)
 {
+    if constexpr (F16 == 0)
+        if (a.col_iters > 2)
+            return (const void *)yuv_rows_kernel<F16, kRowsWidePairs, EXACT, NHWC, GL>;
     return a.col_iters > 1 ? (const void *)yuv_rows_kernel<F16, 2, EXACT, NHWC, GL>
            : a.Cw > 1      ? (const void *)yuv_rows_kernel<F16, 1, EXACT, NHWC, GL>
                       : (const void *)yuv_rows_kernel<F16, 1, EXACT, NHWC | kFormOne, GL>;

@@ -201,3 +201,50 @@ def test_rgb_strip_counts(crop_w, strips):
     """RGB crops run in the fewest strips of up to 256 columns."""
     wl = _rgb([(640, 40), (633, 41)], (16, crop_w), F16, NCHW)
     assert _exact(wl)["work_items"] == 2 * 16 * strips
+
+
+# Crops past one strip of 256 columns: one strip of four column pairs per lane
+# for uniform batches of long rows, interleaved float rows and float I420.
+@pytest.mark.parametrize("crop_w", [257, 258, 300, 385, 511, 512])
+@pytest.mark.parametrize("kind,dtype,layout,strips", [
+    ("long", F32, NCHW, 1), ("long", F16, NCHW, 1), ("long", F32, NHWC, 1), ("long", F16, NHWC, 1),
+    ("long", U8, NCHW, 2), ("ragged", F16, NCHW, 2), ("ragged", F32, NHWC, 2),
+    ("short", F32, NHWC, 1), ("short", F32, NCHW, 2), ("short", F16, NHWC, 2),
+    ("yuv", F32, NCHW, 1), ("yuv", F32, NHWC, 1), ("yuv", F16, NHWC, None)])
+def test_wide_crops(kind, dtype, layout, strips, crop_w):
+    sizes = {"long": [(1200, 30)] * 3, "ragged": [(1200, 30), (1100, 31), (1200, 29)],
+             "short": [(600, 30), (601, 20)], "yuv": [(1280, 30), (1281, 31)]}[kind]
+    wl = (_yuv(sizes, (24, crop_w), dtype, layout, smol.CHROMA_LEFT) if kind == "yuv" else
+          _rgb(sizes, (24, crop_w), dtype, layout))
+    plan = _exact(wl)
+    assert plan["path"] == smol.PATH_ROWS
+    if strips is not None:
+        assert plan["work_items"] == len(sizes) * 24 * strips
+
+
+@pytest.mark.parametrize("order", [1, 2])
+@pytest.mark.parametrize("dtype,layout", [(F32, NCHW), (F16, NCHW), (F32, NHWC), (F16, NHWC)])
+@pytest.mark.parametrize("width", [1200, 600])
+def test_wide_crops_in_either_order(width, dtype, layout, order):
+    """Either row walk of wide crops, uniform and ragged, with both prefetch depths."""
+    for sizes in ([(width, 30)] * 3, [(width, 30), (width - 1, 31)]):
+        for band in (0, 1, 2):
+            _exact(_rgb(sizes, (24, 300), dtype, layout), row_order=order, band_rows=band)
+
+
+# The default arithmetic: one unit in the last place of the result (fp32: the
+# product with RN(1/std) against the quotient; fp16: one rounding instead of two).
+@pytest.mark.parametrize("crop", [(64, 72), (64, 131), (64, 224), (64, 300), (40, 513), (24, 640)])
+@pytest.mark.parametrize("layout", [NCHW, NHWC])
+@pytest.mark.parametrize("dtype", [F32, F16, U8])
+@pytest.mark.parametrize("kind", ["rgb", "long", "yuv"])
+def test_default_arithmetic(kind, dtype, layout, crop):
+    sizes = [(300, 90), (301, 200), (64, 33)] if kind != "long" else [(1300, 70), (1299, 64)]
+    wl = (_yuv(sizes, crop, dtype, layout, smol.CHROMA_CENTER) if kind == "yuv" else
+          _rgb(sizes, crop, dtype, layout))
+    got, ref = run_gpu(wl), run_oracle(wl)
+    if dtype == U8:
+        np.testing.assert_array_equal(got, ref)
+        return
+    ulp = np.maximum(np.spacing(np.abs(ref)), np.spacing(np.abs(got))).astype(np.float64)
+    assert (np.abs(got.astype(np.float64) - ref.astype(np.float64)) <= ulp).all()
