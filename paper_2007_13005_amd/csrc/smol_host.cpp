@@ -587,11 +587,14 @@ int run_batch(const std::vector<Desc> &descs, size_t first, size_t count, int no
                        (order == 2 || (order == 0 && uniform && a.row_groups >= 4 &&
                                        a.strips <= 2));
         // Whole-line stores: rows of 16-byte multiples, at least one line
-        // long, that are not whole lines themselves, in planes of whole lines.
+        // long, that are not whole lines themselves, in planes of whole lines,
+        // where the rings fit the caller's LDS budget (0: none) as well.
+        const int budget = g_lds_budget.load();
         const long long rb = 2LL * a.Cw;
         a.lines = pl.path == smol::PATH_ROWS && pl.f16 == SMOL_OUT_F16 && !a.interleave &&
                   !a.nhwc && a.Cw <= smol::kStripCols && a.strips == 1 && rb % 16 == 0 && rb >= 128 && rb % 128 != 0 &&
-                  rb * a.Ch % 128 == 0 && ((uintptr_t)a.out & 127) == 0;
+                  rb * a.Ch % 128 == 0 && ((uintptr_t)a.out & 127) == 0 &&
+                  (budget == 0 || pl.lds_bytes + 3 * smol::kLineRing <= (size_t)budget);
         if (a.lines)
             pl.lds_bytes += 3 * smol::kLineRing;
     }

@@ -248,3 +248,9 @@ def test_default_arithmetic(kind, dtype, layout, crop):
         return
     ulp = np.maximum(np.spacing(np.abs(ref)), np.spacing(np.abs(got))).astype(np.float64)
     assert (np.abs(got.astype(np.float64) - ref.astype(np.float64)) <= ulp).all()
+
+
+@pytest.mark.parametrize("budget,lds", [(4096, 4096), (7167, 4096), (7168, 7168), (0, 7168)])
+def test_line_rings_within_the_lds_budget(budget, lds):
+    wl = _rgb([(500, 40), (501, 33)], (64, 224), F16, NCHW)
+    assert _exact(wl, path=smol.PATH_ROWS, lds_budget=budget)["lds_bytes"] == lds
