@@ -17,7 +17,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libsmol.so")
-PYCALL = os.path.join(PKG, "_smolcall.so")  # the binding's native marshalling
+# the binding's native marshalling, named for this interpreter's ABI
+PYCALL = os.path.join(PKG, "_smolcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 # The row-streaming kernels are split into parts (input, output type, row
 # walk, output layout) so that the compiler runs on the parts in parallel.

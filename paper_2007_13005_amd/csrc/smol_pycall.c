@@ -5,7 +5,7 @@
  * call(address, *args) calls the C function at `address` with up to 18
  * integer or pointer arguments and returns its int result: None is a null
  * pointer or zero, an int itself, any other object the address of its
- * contiguous buffer (numpy arrays, ctypes structures), held for the call. The
+ * C-contiguous buffer (numpy arrays, ctypes structures), held for the call. The
  * GIL is released meanwhile. An ABI function takes only such arguments, which
  * the x86-64 System V convention passes in 64-bit registers and stack slots.
  *
@@ -50,8 +50,15 @@ static PyObject *call(PyObject *self, PyObject *const *args, Py_ssize_t nargs)
             ok = overflow >= 0 && !PyErr_Occurred();
             if (overflow < 0)
                 PyErr_SetString(PyExc_OverflowError, "integer argument below -2^63");
-        } else if (PyObject_GetBuffer(o, &views[nviews], PyBUF_SIMPLE) == 0) {
-            a[i - 1] = (w)(intptr_t)views[nviews++].buf;
+        } else if (PyObject_GetBuffer(o, &views[nviews], PyBUF_ND) == 0) {
+            const Py_buffer *v = &views[nviews++];
+            a[i - 1] = (w)(intptr_t)v->buf;
+            if (v->ndim == 0 && PyIndex_Check(o)) {
+                /* a numpy integer: a number whose address nobody means */
+                PyErr_Format(PyExc_TypeError, "argument %zd is a %.80s, not an int", i,
+                             Py_TYPE(o)->tp_name);
+                ok = 0;
+            }
         } else {
             ok = 0;
         }

@@ -407,6 +407,14 @@ def _launch_stream(stream, *tensors) -> int:
     return st.cuda_stream
 
 
+def _struct_types(params, options) -> None:
+    """The structures go to the library by address (_call): no other objects."""
+    if not isinstance(params, Params):
+        raise TypeError(f"params must be a Params, not {type(params).__name__}")
+    if options is not None and not isinstance(options, Options):
+        raise TypeError(f"options must be an Options or None, not {type(options).__name__}")
+
+
 def _out_tensor(out, n: int, params: Params, device, layout: int = LAYOUT_NCHW):
     _load_modules()
     torch = _torch
@@ -450,6 +458,7 @@ def preprocess_batch(src, offsets, widths, heights, params: Params, pitches=None
     if not (len(w) == len(h) == n and (pt is None or len(pt) == n)):
         raise ValueError("table lengths differ")
     r = _rois(rois, n)
+    _struct_types(params, options)
     out = _out_tensor(out, n, params, src.device, options.layout if options else LAYOUT_NCHW)
     if r is None and options is None:
         _call("smol_preprocess_batch", src.data_ptr(), src.numel(), off, w, h, pt, n, params,
@@ -476,6 +485,7 @@ def yuv420_preprocess_batch(src, y_offsets, cb_offsets, cr_offsets, widths, heig
     if not (len(bo) == len(ro) == len(w) == len(h) == n):
         raise ValueError("table lengths differ")
     r = _rois(rois, n)
+    _struct_types(params, options)
     out = _out_tensor(out, n, params, src.device, options.layout if options else LAYOUT_NCHW)
     if r is None and options is None:
         _call("smol_yuv420_preprocess_batch", src.data_ptr(), src.numel(), yo, bo, ro, w, h, n,
@@ -515,6 +525,7 @@ def lowres_preprocess_batch(src, offsets, widths, heights, params: Params, low_r
     n = len(off)
     if not (len(w) == len(h) == n and (pt is None or len(pt) == n)):
         raise ValueError("table lengths differ")
+    _struct_types(params, None)
     out = _out_tensor(out, n, params, src.device)
     ws = _workspace(workspace, n, low_res, src.device)
     _call("smol_lowres_preprocess_batch", src.data_ptr(), src.numel(), off, w, h, pt, n,
@@ -537,6 +548,7 @@ def yuv420_lowres_preprocess_batch(src, y_offsets, cb_offsets, cr_offsets, width
     n = len(yo)
     if not (len(bo) == len(ro) == len(w) == len(h) == n):
         raise ValueError("table lengths differ")
+    _struct_types(params, None)
     out = _out_tensor(out, n, params, src.device)
     ws = _workspace(workspace, n, low_res, src.device)
     _call("smol_yuv420_lowres_preprocess_batch", src.data_ptr(), src.numel(), yo, bo, ro, w, h,
@@ -617,6 +629,7 @@ def jpeg_roi_preprocess_batch(coef, coef_offsets, qtables, widths, heights, para
     need = jpeg_workspace_bytes(w, h)
     if workspace is None:
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=coef.device)
+    _struct_types(params, options)
     out = _out_tensor(out, n, params, coef.device, options.layout if options else LAYOUT_NCHW)
     _call("smol_jpeg_roi_preprocess_batch", coef.data_ptr(), coef.numel(), co, q, nq, w, h, n,
           operator.index(coef_layout), params, options, workspace.data_ptr(), workspace.numel(),

@@ -524,3 +524,63 @@ def test_mcu_rect_checks_params_like_the_batch_calls(kw, mode):
     rc = smol.lib().smol_jpeg_mcu_rect(640, 480, ctypes.byref(p),
                                        ctypes.byref(smol.make_options(mode)), rect.ctypes.data)
     assert rc == smol.ERR_INVALID_ARG
+
+
+# The binding's native call: a callback that records the words it is passed.
+WORDS = 18
+
+
+@pytest.fixture
+def native():
+    from paper_2007_13005_amd import _smolcall
+    seen = []
+
+    def record(*words):
+        seen.append(words)
+        return -7
+
+    cb = ctypes.CFUNCTYPE(ctypes.c_int, *[ctypes.c_int64] * WORDS)(record)
+    address = ctypes.cast(cb, ctypes.c_void_p).value
+    return lambda *args: (_smolcall.call(address, *args), seen[-1]), seen, cb
+
+
+def test_native_call_arguments(native):
+    call, _, _ = native
+    table = np.arange(6, dtype=np.int32).reshape(2, 3)
+    params = _params()
+    result, words = call(None, -5, 2**63 + 9, table, params, np.zeros((), np.int64)[None], 1)
+    assert result == -7
+    assert words[:5] == (0, -5, 9 - 2**63, table.ctypes.data, ctypes.addressof(params))
+    assert words[6] == 1 and words[7:] == (0,) * (WORDS - 7)
+
+
+@pytest.mark.parametrize("bad,error", [
+    (np.int64(3), TypeError), (np.int32(3), TypeError), (np.array(3), TypeError),
+    (np.zeros((4, 4))[:, ::2], (BufferError, ValueError)), (3.5, TypeError), ("x", TypeError),
+    (-2**63 - 1, OverflowError), (2**64, OverflowError)])
+def test_native_call_refuses(native, bad, error):
+    call, seen, _ = native
+    held = bytearray(8)
+    with pytest.raises(error):
+        call(held, bad)
+    assert not seen
+    held.append(1)  # its buffer was released
+
+
+def test_native_call_argument_count(native):
+    call, _, _ = native
+    assert call(*range(WORDS))[1] == tuple(range(WORDS))
+    with pytest.raises(TypeError):
+        call(*range(WORDS + 1))
+
+
+def test_structures_are_checked():
+    class Look:
+        out_dtype = smol.OUT_F16
+
+    for params, options in ((Look(), None), (smol.make_options(), None), (_params(), _params()),
+                            (_params(), 0), (None, None)):
+        with pytest.raises(TypeError):
+            smol._struct_types(params, options)
+    smol._struct_types(_params(), None)
+    smol._struct_types(_params(), smol.make_options())
