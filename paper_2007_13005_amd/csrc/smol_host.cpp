@@ -394,16 +394,19 @@ struct Plan {
 //     set-up and a load latency per row, and what overlaps is computed and
 //     stored twice: 48 photos of 1556 x 1037 to 316 x 316 take 25.0 us in 2
 //     strips of 160 and 29.4 in 3 of 128, 128 of 640 x 480 to 448 x 448 62.7 in 2
-//     of 224 and 66.4 in 2 of 256 (float 91.2 and 104.3), 16 of 720p to 896 x
-//     512 22.0 in 4 of 224 and 23.3 in 7 of 128, 32 of 720p to 640 x 640 40.4
-//     in 3 of 224 and 40.8 in 5 of 128.
+//     of 224 and 66.4 in 2 of 256 (float 91.2 and 104.3). But 128 where that
+//     gives whole fp16 lines and equal widths do not: with inputs and outputs
+//     that change from call to call, 32 of 720p to 640 x 640 take 33.2 in 5 of 128
+//     and 39.5 in 3 of 224 (float 47.2 and 52.0), 16 to 896 x 896 24.7 in 7 of
+//     128 and 24.4 in 4 of 224 (float 33.5 and 34.2).
 // More strips than that (long source spans) have equal widths.
 void plan_strips(int Cw, bool rgb, int least, int *strips, int *strip_w)
 {
     const int halves = (Cw + 127) / 128, fewest = (halves + 1) / 2;
     const int unit = Cw % 32 == 0 ? 32 : 4;
+    const int even = ((Cw + fewest - 1) / fewest + unit - 1) / unit * unit;
     const int width = Cw <= smol::kStripCols ? Cw
-                      : rgb          ? ((Cw + fewest - 1) / fewest + unit - 1) / unit * unit
+                      : rgb && (Cw % 128 != 0 || even % 64 == 0) ? even
                       : halves % 2   ? 128
                                      : smol::kStripCols;
     *strips = (Cw + width - 1) / width;

@@ -196,9 +196,10 @@ def test_long_rows_in_ranges(width, layout, dtype):
 
 
 @pytest.mark.parametrize("crop_w,strips", [(300, 2), (384, 2), (448, 2), (512, 2), (600, 3),
-                                           (640, 3), (768, 3), (896, 4), (1024, 4)])
+                                           (640, 5), (768, 3), (896, 7), (1024, 4)])
 def test_rgb_strip_counts(crop_w, strips):
-    """RGB crops run in the fewest strips of up to 256 columns."""
+    """RGB crops run in the fewest strips of up to 256 columns, or in strips of
+    128 where only those are whole fp16 lines."""
     wl = _rgb([(640, 40), (633, 41)], (16, crop_w), F16, NCHW)
     assert _exact(wl)["work_items"] == 2 * 16 * strips
 
