@@ -347,7 +347,8 @@ int smol_image_geometry_ex(int32_t width, int32_t height, int32_t yuv420, const 
  *               budget twice, else SMOL_ERR_UNSUPPORTED; images whose 16-byte
  *               source chunks cross an end of src use the direct kernel);
  *               0: automatic (RGB: row-streaming when it fits, in column
- *               strips for crops up to 2048 columns or longer spans unless
+ *               strips of at least 48 columns for crops up to 2048 columns
+ *               or longer spans of at least half of the images, unless
  *               lds_budget is set, else register-gather when its tables fit,
  *               else LDS-staged when the span fits, else direct; I420:
  *               row-streaming when the crop is at most 512 columns, the luma

@@ -25,7 +25,7 @@
 // and 81 MB of pixels, 47 us at a large copy's 5.05 TB/s. 59.5 us with one
 // group of eight per job, 4-byte stores of 64-byte row pieces and every
 // output's products formed on their own (194 vector and 110 scalar instructions
-// per group), 48 us now (about 155 and 45); with nontemporal coefficient loads
+// per group), 48 us now (170 and 84); with nontemporal coefficient loads
 // the planes stay cached for the preprocessing that reads them next (2 us of
 // the pair of launches; nontemporal stores cost it 1.5).
 #include <hip/hip_runtime.h>

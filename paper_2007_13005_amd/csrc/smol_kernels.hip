@@ -883,8 +883,8 @@ static size_t yuv_rows_table_lds(const BatchArgs &a, bool uniform)
 int launch_yuv_rows(const BatchArgs &a, int out_f16, size_t lds_bytes, void *stream, void *done)
 {
     return launch_one(yuv_rows_kernel_for(a, out_f16),
-                      dim3((unsigned)(a.grid / a.wpg), (unsigned)a.strips), dim3(64 * a.wpg), lds_bytes * a.wpg + yuv_rows_table_lds(a, !a.table), a,
-                      stream, done);
+                      dim3((unsigned)(a.grid / a.wpg), (unsigned)a.strips), dim3(64 * a.wpg),
+                      lds_bytes * a.wpg + yuv_rows_table_lds(a, !a.table), a, stream, done);
 }
 
 int occupancy_yuv_rows(const BatchArgs &a, int out_f16, size_t lds_bytes, int *blocks_per_cu)

@@ -534,9 +534,8 @@ __device__ __forceinline__ void read_row_taps(uint32_t row, const int (&cx)[J][2
         A[t] = row + (uint32_t)cx[t / 2][t & 1];
         ad[t] = A[t] & ~3u;
     }
-    if constexpr (N == 8)
-        lds_read_taps8(ad, lo, hi);
-    else if constexpr (N == 4)
+    static_assert(N == 2 || N == 4, "lerps are kept for one or two pairs per lane");
+    if constexpr (N == 4)
         lds_read_taps4(ad, lo, hi);
     else
         lds_read_taps2(ad, lo, hi);

@@ -278,32 +278,32 @@ __global__ void __launch_bounds__(64 * kRowsMaxWavesPerGroup) rgb_range_kernel(B
     bool swap = false;  // hB holds y0's lerps, hA y1's
     RowOut<F16, J> out;
     auto compute = [&](const RowS &row) {
-        if constexpr (J > 2) {
+        if constexpr (J > 2) {  // (kept lerps would take 48 registers more)
             rows_compute<F16, J, EXACT>(nk, lds0 + row.sh0, lds1 + row.sh1, row.wy, cx, cw, out);
-            return;
-        }
-        if (row.rel == kRowNew) {
-            swap = false;
-            rows_horizontal<J>(lds0 + row.sh0, cx, cw, hA);
-            rows_horizontal<J>(lds1 + row.sh1, cx, cw, hB);
-        } else if (row.rel == kRowShift) {
-            // (the differing empty asm keeps the branches apart: merged into
-            // one with a chosen array, the arrays would live in memory)
-            swap = !swap;
-            if (swap) {
-                rows_horizontal<J>(lds1 + row.sh1, cx, cw, hA);
-                asm volatile("; row into A");
-            } else {
-                rows_horizontal<J>(lds1 + row.sh1, cx, cw, hB);
-                asm volatile("; row into B");
-            }
-        }
-        if (swap) {
-            rows_vertical<F16, J, EXACT>(nk, hB, hA, row.wy, out);
-            asm volatile("; rows B, A");
         } else {
-            rows_vertical<F16, J, EXACT>(nk, hA, hB, row.wy, out);
-            asm volatile("; rows A, B");
+            if (row.rel == kRowNew) {
+                swap = false;
+                rows_horizontal<J>(lds0 + row.sh0, cx, cw, hA);
+                rows_horizontal<J>(lds1 + row.sh1, cx, cw, hB);
+            } else if (row.rel == kRowShift) {
+                // (the differing empty asm keeps the branches apart: merged into
+                // one with a chosen array, the arrays would live in memory)
+                swap = !swap;
+                if (swap) {
+                    rows_horizontal<J>(lds1 + row.sh1, cx, cw, hA);
+                    asm volatile("; row into A");
+                } else {
+                    rows_horizontal<J>(lds1 + row.sh1, cx, cw, hB);
+                    asm volatile("; row into B");
+                }
+            }
+            if (swap) {
+                rows_vertical<F16, J, EXACT>(nk, hB, hA, row.wy, out);
+                asm volatile("; rows B, A");
+            } else {
+                rows_vertical<F16, J, EXACT>(nk, hA, hB, row.wy, out);
+                asm volatile("; rows A, B");
+            }
         }
     };
     // Whole lines: the ring holds byte b of the wave's rows (counted from

@@ -32,17 +32,18 @@ namespace {
 // weight bytes; the BT.601 products then use the coefficients divided by 16,
 // which gives the same real products and so the same rounded values.
 //
-// Lane l computes J pairs of output columns (pair_col). Per column it keeps: the luma tap (offset of x0 in the staged luma span, weight), and
-// for its two luma columns x0, x1 the offset of the first chroma column they
-// read, per luma column a v_perm selector that picks its two chroma samples
-// from each of two chroma rows, and its horizontal weight bytes
-// (4 - fx, fx).
+// Lane l computes J pairs of output columns (pair_col). Per column it keeps: the
+// luma tap (offset of x0 in the staged luma span, weight), and for its two luma
+// columns x0, x1 the offset of the first chroma column they read, per luma column
+// a v_perm selector that picks its two chroma samples from each of two chroma
+// rows, and its horizontal weight bytes (4 - fx, fx).
 //
 // Bound by VALU issue: without its loads and stores it takes as long (128
-// frames of 720p: 32.1 us, 32.4 without either, 10.8 without the arithmetic).
-// 462 of a row's 495 vector instructions are the definition's arithmetic and
-// the reads; with the rows' taps computed 64 at a time the walk takes 35 and 116
-// scalar ones (64 and 199 with a cursor): 32.0 -> 31.5 us, 4K strips 17.4 -> 17.1.
+// frames of 720p: 32.1 us, 32.4 without either, 10.8 without the arithmetic), and
+// its waves issue vector instructions for 0.33 of their cycles, at three waves
+// per SIMD (waiting for LDS 0.06, ready and not issued 0.29). Set-up included a
+// row takes 528 vector and 133 scalar instructions (the latter with the rows' taps
+// computed 64 at a time: 31.5 us, 32.0 with a cursor; 4K strips 17.1 and 17.4).
 // Loading after the stores' row is staged (as for RGB), 2 or 4 waves per SIMD and
 // the ILP scheduler are no faster.
 // ---------------------------------------------------------------------------
@@ -605,8 +606,10 @@ __attribute__((amdgpu_waves_per_eu(J > 2 ? 2 : 3))) yuv_rows_kernel(BatchArgs a)
     {
         const YuvImg g = yuv_img(a, c_img, strip);
         if (!a.table && a.wpg > 1)
-            yuv_cols_shared<J, QUADS>(cols, lds_all + a.wpg * yuv_seg<GL>(8), g, a.strip_w, lane, a.siting,
-                               __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), a.wpg);
+            yuv_cols_shared<J, QUADS>(cols, lds_all + a.wpg * yuv_seg<GL>(8), g, a.strip_w, lane,
+                                      a.siting,
+                                      __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)),
+                                      a.wpg);
         else
             yuv_cols<J, QUADS>(cols, g, a.strip_w, lane, a.siting);
         cW = g.W;
