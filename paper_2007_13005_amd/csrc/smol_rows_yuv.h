@@ -41,11 +41,11 @@ namespace {
 // Bound by VALU issue: without its loads and stores it takes as long (128
 // frames of 720p: 32.1 us, 32.4 without either, 10.8 without the arithmetic), and
 // its waves issue vector instructions for 0.33 of their cycles, at three waves
-// per SIMD (waiting for LDS 0.06, ready and not issued 0.29). Set-up included a
-// row takes 528 vector and 133 scalar instructions (the latter with the rows' taps
+// per SIMD (waiting for counters, LDS among them, 0.22; ready and not issued 0.29).
+// Set-up included a row takes 528 vector and 133 scalar instructions (the latter with the rows' taps
 // computed 64 at a time: 31.5 us, 32.0 with a cursor; 4K strips 17.1 and 17.4).
-// Loading after the stores' row is staged (as for RGB), 2 or 4 waves per SIMD and
-// the ILP scheduler are no faster.
+// Loading after the row is staged, 2 or 4 waves per SIMD and the ILP scheduler are
+// no faster.
 // ---------------------------------------------------------------------------
 // A frame's plane offsets and the processed region: W x H luma pixels at
 // (rx, ry) in a frame of fw x fh (chroma taps use frame coordinates).
