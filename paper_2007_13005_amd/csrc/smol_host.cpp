@@ -1025,15 +1025,18 @@ static int rgb_batch(const uint8_t *src, int64_t src_bytes, const int64_t *offse
                                            p->crop_w <= smol::kStripsMaxCols);
         // Crops past kStripCols columns in one strip, four column pairs per lane,
         // where strips are slower: the strided walk of long rows (32 frames of 720p
-        // to 300 x 300 20.1 us and 21.7 in strips, to 448 x 448 25.2 and 26.6) and
-        // interleaved float rows (128 of 640 x 480 to 448 x 448 103 and 108). (The
-        // kernels have these instances only: kRowsWidePairs.)
+        // to 300 x 300 20.1 us and 21.7 in strips, to 448 x 448 25.2 and 26.6),
+        // uint8 from long rows (96 photos of 800 to 1350 to 448 x 448 72.7 and 82.6,
+        // to 320 x 320 52.5 and 57.4) and interleaved float rows (128 of 640 x 480
+        // to 448 x 448 103 and 108). (The kernels have these instances only:
+        // kRowsWidePairs.)
         int64_t stride = 0;
         const int order = g_row_order.load();
         const bool one_strip =
             rows_ok && p->crop_w > smol::kStripCols &&
-            (groups > 2 ? order != 1 && f16 != SMOL_OUT_U8 &&
-                              (order == 2 || is_uniform(descs, 0, (size_t)n, 1, &stride))
+            (groups > 2 ? f16 == SMOL_OUT_U8 ||
+                              (order != 1 &&
+                               (order == 2 || is_uniform(descs, 0, (size_t)n, 1, &stride)))
                         : order != 2 && f16 == SMOL_OUT_F32 && a.nhwc);
         int64_t strip_cols = 0;
         if (strips_ok && (forced == smol::PATH_ROWS ||

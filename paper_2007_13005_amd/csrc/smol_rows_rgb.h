@@ -389,7 +389,7 @@ const void *rgb_rows_g(const BatchArgs &a)
             return a.col_iters > 1 ? rgb_rows_k<F16, EXACT, G, STRIDE, kFormLines, 2>(a)
                                    : rgb_rows_k<F16, EXACT, G, STRIDE, kFormLines, 1>(a);
     // (the forms that the host's plan takes to one wide strip)
-    if constexpr (STRIDE ? G == 4 : F16 == 0 && NHWC && G <= 2)
+    if constexpr (STRIDE || F16 == 2 ? G == 4 : F16 == 0 && NHWC && G <= 2)
         if (a.col_iters > 2)
             return rgb_rows_k<F16, EXACT, G, STRIDE, NHWC, kRowsWidePairs>(a);
     return a.col_iters > 1 ? rgb_rows_k<F16, EXACT, G, STRIDE, NHWC, 2>(a)

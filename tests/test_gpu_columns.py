@@ -205,11 +205,13 @@ def test_rgb_strip_counts(crop_w, strips):
 
 
 # Crops past one strip of 256 columns: one strip of four column pairs per lane
-# for uniform batches of long rows, interleaved float rows and float I420.
+# for uniform batches and uint8 output of long rows, interleaved float rows and
+# float I420.
 @pytest.mark.parametrize("crop_w", [257, 258, 300, 385, 511, 512])
 @pytest.mark.parametrize("kind,dtype,layout,strips", [
     ("long", F32, NCHW, 1), ("long", F16, NCHW, 1), ("long", F32, NHWC, 1), ("long", F16, NHWC, 1),
-    ("long", U8, NCHW, 2), ("ragged", F16, NCHW, 2), ("ragged", F32, NHWC, 2),
+    ("long", U8, NCHW, 1), ("ragged", U8, NCHW, 1), ("ragged", U8, NHWC, 1),
+    ("short", U8, NHWC, 2), ("ragged", F16, NCHW, 2), ("ragged", F32, NHWC, 2),
     ("short", F32, NHWC, 1), ("short", F32, NCHW, 2), ("short", F16, NHWC, 2),
     ("yuv", F32, NCHW, 1), ("yuv", F32, NHWC, 1), ("yuv", F16, NHWC, None)])
 def test_wide_crops(kind, dtype, layout, strips, crop_w):
